@@ -1639,8 +1639,12 @@ dvnr_status dvnr_mlp_forward(dvnr_t* h, int32_t block, int64_t n, const void* fe
   if (st) return st;
   if (n < 0 || (n > 0 && (!feats || !out))) return fail(DVNR_E_INVALID, "bad arguments");
   if (!weights) weights = block_elem(h, h->buf.params, block, h->n_table);
-  const Prec p = h->prec == Prec::F64 ? Prec::F64 : Prec::F32;
-  HIPCHK(launch_mlp_simple_fwd(p, h->md, n, feats, weights, out, (hipStream_t)stream));
+  if (h->prec == Prec::F64)
+    HIPCHK(launch_mlp_simple_fwd(h->md, n, (const double*)feats, (const double*)weights, (double*)out,
+                                 (hipStream_t)stream));
+  else
+    HIPCHK(launch_mlp_block_fwd(h->md, n, (const float*)feats, (const float*)weights, (float*)out,
+                                (hipStream_t)stream));
   return DVNR_OK;
 }
 
@@ -1651,8 +1655,12 @@ dvnr_status dvnr_mlp_backward(dvnr_t* h, int32_t block, int64_t n, const void* f
   if (n < 0 || (n > 0 && (!feats || !dout || !dfeats))) return fail(DVNR_E_INVALID, "bad arguments");
   if (!weights) weights = block_elem(h, h->buf.params, block, h->n_table);
   if (!dweights) dweights = block_elem(h, h->buf.grads, block, h->n_table);
-  const Prec p = h->prec == Prec::F64 ? Prec::F64 : Prec::F32;
-  HIPCHK(launch_mlp_simple_bwd(p, h->md, n, feats, weights, dout, dfeats, dweights, (hipStream_t)stream));
+  if (h->prec == Prec::F64)
+    HIPCHK(launch_mlp_simple_bwd(h->md, n, (const double*)feats, (const double*)weights, (const double*)dout,
+                                 (double*)dfeats, (double*)dweights, (hipStream_t)stream));
+  else
+    HIPCHK(launch_mlp_block_bwd(h->md, n, (const float*)feats, (const float*)weights, (const float*)dout,
+                                (float*)dfeats, (float*)dweights, (hipStream_t)stream));
   return DVNR_OK;
 }
 

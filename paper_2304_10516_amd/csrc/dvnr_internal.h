@@ -240,11 +240,16 @@ hipError_t launch_adam(Prec p, void* params, void* grad, void* m, void* v, uint1
                        double decay_base, int64_t decay_start, int64_t decay_interval, hipStream_t s,
                        int64_t skip0 = 0, int64_t skip1 = 0);
 
-// Reference-style building blocks (thread per sample) for the autograd pieces.
-hipError_t launch_mlp_simple_fwd(Prec p, const MlpDesc& md, int64_t n, const void* feats, const void* w,
-                                 void* out, hipStream_t s);
-hipError_t launch_mlp_simple_bwd(Prec p, const MlpDesc& md, int64_t n, const void* feats, const void* w,
-                                 const void* dout, void* dfeats, void* dw, hipStream_t s);
+// MLP building blocks for the autograd pieces: fp32 on MFMA, and fp64 with one
+// thread per sample.  feats, dfeats [n][in]; dw is added to.
+hipError_t launch_mlp_block_fwd(const MlpDesc& md, int64_t n, const float* feats, const float* w, float* out,
+                                hipStream_t s);
+hipError_t launch_mlp_block_bwd(const MlpDesc& md, int64_t n, const float* feats, const float* w, const float* dout,
+                                float* dfeats, float* dw, hipStream_t s);
+hipError_t launch_mlp_simple_fwd(const MlpDesc& md, int64_t n, const double* feats, const double* w, double* out,
+                                 hipStream_t s);
+hipError_t launch_mlp_simple_bwd(const MlpDesc& md, int64_t n, const double* feats, const double* w,
+                                 const double* dout, double* dfeats, double* dw, hipStream_t s);
 
 // Fused decode of one block (voxel centers, encoding through LDS-staged vertex
 // boxes, MLP forward); table / wsrc point at element 0 of the parameter index

@@ -641,96 +641,84 @@ hipError_t launch_mlp_infer(Prec p, const MlpDesc& md, const LevelDesc& ld, cons
 }
 
 // ---------------------------------------------------------------------------
-// Simple thread-per-sample MLP (autograd building blocks, any precision).
+// Simple thread-per-sample MLP (fp64 autograd building blocks).
 // feats [n][in], weights [n_mlp] (block layout), out [n].
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(128) void k_mlp_simple_fwd(MlpDesc md, int64_t n, const T* __restrict__ x,
-                                                        const T* __restrict__ w, T* __restrict__ out) {
+__global__ __launch_bounds__(128) void k_mlp_simple_fwd(MlpDesc md, int64_t n, const double* __restrict__ x,
+                                                        const double* __restrict__ w, double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  T a[64], b[64];
+  double a[64], b[64];
   const int in = md.in_dim, W = md.width;
   for (int k = 0; k < in; ++k) a[k] = x[i * in + k];
   int cur = in;
   for (int layer = 0; layer < md.n_hidden; ++layer) {
-    const T* M = w + md.off[layer];
+    const double* M = w + md.off[layer];
     for (int r = 0; r < W; ++r) {
-      T s = 0;
+      double s = 0;
       for (int k = 0; k < cur; ++k) s += M[r * cur + k] * a[k];
-      b[r] = s > T(0) ? s : T(0);
+      b[r] = s > 0.0 ? s : 0.0;
     }
     for (int r = 0; r < W; ++r) a[r] = b[r];
     cur = W;
   }
-  T s = 0;
+  double s = 0;
   for (int k = 0; k < W; ++k) s += w[md.off[md.n_hidden] + k] * a[k];
   out[i] = s;
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void k_mlp_simple_bwd(MlpDesc md, int64_t n, const T* __restrict__ x,
-                                                       const T* __restrict__ w, const T* __restrict__ dout,
-                                                       T* __restrict__ dx, T* __restrict__ dw) {
+__global__ __launch_bounds__(64) void k_mlp_simple_bwd(MlpDesc md, int64_t n, const double* __restrict__ x,
+                                                       const double* __restrict__ w, const double* __restrict__ dout,
+                                                       double* __restrict__ dx, double* __restrict__ dw) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int in = md.in_dim, W = md.width, NH = md.n_hidden;
-  T act[5][64];  // act[0] = input, act[k] = output of hidden layer k
+  double act[5][64];  // act[0] = input, act[k] = output of hidden layer k
   for (int k = 0; k < in; ++k) act[0][k] = x[i * in + k];
   for (int layer = 0; layer < NH; ++layer) {
     const int cur = layer == 0 ? in : W;
-    const T* M = w + md.off[layer];
+    const double* M = w + md.off[layer];
     for (int r = 0; r < W; ++r) {
-      T s = 0;
+      double s = 0;
       for (int k = 0; k < cur; ++k) s += M[r * cur + k] * act[layer][k];
-      act[layer + 1][r] = s > T(0) ? s : T(0);
+      act[layer + 1][r] = s > 0.0 ? s : 0.0;
     }
   }
-  const T d = dout[i];
-  T g[64], gn[64];
-  const T* wo = w + md.off[NH];
+  const double d = dout[i];
+  double g[64], gn[64];
+  const double* wo = w + md.off[NH];
   for (int r = 0; r < W; ++r) {
     unsafeAtomicAdd(&dw[md.off[NH] + r], d * act[NH][r]);
-    g[r] = act[NH][r] > T(0) ? wo[r] * d : T(0);
+    g[r] = act[NH][r] > 0.0 ? wo[r] * d : 0.0;
   }
   for (int layer = NH - 1; layer >= 0; --layer) {
     const int cur = layer == 0 ? in : W;
-    const T* M = w + md.off[layer];
+    const double* M = w + md.off[layer];
     for (int r = 0; r < W; ++r)
       for (int k = 0; k < cur; ++k) unsafeAtomicAdd(&dw[md.off[layer] + r * cur + k], g[r] * act[layer][k]);
     for (int k = 0; k < cur; ++k) {
-      T s = 0;
+      double s = 0;
       for (int r = 0; r < W; ++r) s += M[r * cur + k] * g[r];
-      gn[k] = (layer == 0 || act[layer][k] > T(0)) ? s : T(0);
+      gn[k] = (layer == 0 || act[layer][k] > 0.0) ? s : 0.0;
     }
     for (int k = 0; k < cur; ++k) g[k] = gn[k];
   }
   for (int k = 0; k < in; ++k) dx[i * in + k] = g[k];
 }
 
-hipError_t launch_mlp_simple_fwd(Prec p, const MlpDesc& md, int64_t n, const void* feats, const void* w, void* out,
+hipError_t launch_mlp_simple_fwd(const MlpDesc& md, int64_t n, const double* feats, const double* w, double* out,
                                  hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const unsigned grid = (unsigned)((n + 127) / 128);
-  if (p == Prec::F64)
-    hipLaunchKernelGGL(k_mlp_simple_fwd<double>, dim3(grid), dim3(128), 0, s, md, n, (const double*)feats,
-                       (const double*)w, (double*)out);
-  else
-    hipLaunchKernelGGL(k_mlp_simple_fwd<float>, dim3(grid), dim3(128), 0, s, md, n, (const float*)feats,
-                       (const float*)w, (float*)out);
+  hipLaunchKernelGGL(k_mlp_simple_fwd, dim3(grid), dim3(128), 0, s, md, n, feats, w, out);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_simple_bwd(Prec p, const MlpDesc& md, int64_t n, const void* feats, const void* w,
-                                 const void* dout, void* dfeats, void* dw, hipStream_t s) {
+hipError_t launch_mlp_simple_bwd(const MlpDesc& md, int64_t n, const double* feats, const double* w,
+                                 const double* dout, double* dfeats, double* dw, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const unsigned grid = (unsigned)((n + 63) / 64);
-  if (p == Prec::F64)
-    hipLaunchKernelGGL(k_mlp_simple_bwd<double>, dim3(grid), dim3(64), 0, s, md, n, (const double*)feats,
-                       (const double*)w, (const double*)dout, (double*)dfeats, (double*)dw);
-  else
-    hipLaunchKernelGGL(k_mlp_simple_bwd<float>, dim3(grid), dim3(64), 0, s, md, n, (const float*)feats,
-                       (const float*)w, (const float*)dout, (float*)dfeats, (float*)dw);
+  hipLaunchKernelGGL(k_mlp_simple_bwd, dim3(grid), dim3(64), 0, s, md, n, feats, w, dout, dfeats, dw);
   return hipGetLastError();
 }
 
