@@ -1614,8 +1614,10 @@ dvnr_status dvnr_encode_forward(dvnr_t* h, int32_t block, int64_t n, const float
   if (!table) table = block_elem(h, h->buf.params, block, 0);
   const int64_t LF = h->md.in_dim;
   const Prec tp = h->prec == Prec::F64 ? Prec::F64 : Prec::F32;
+  // XCD-aware: each XCD's L2 holds the tables of two levels, as in training
+  // (2^16 points, 16 levels of 2^17 fp32 entries: 56 -> 28 us against the plain mapping)
   HIPCHK(launch_encode(tp, tp == Prec::F64 ? 2 : 0, h->ld, nullptr, nullptr, (int)n, 0, nullptr, coords, table, feats,
-                       LF, h->enc.n_features, 0, (hipStream_t)stream));
+                       LF, h->enc.n_features, h->xcd_map, (hipStream_t)stream));
   return DVNR_OK;
 }
 
@@ -1627,9 +1629,12 @@ dvnr_status dvnr_encode_backward(dvnr_t* h, int32_t block, int64_t n, const floa
   if (!dtable) dtable = block_elem(h, h->buf.grads, block, 0);
   const int64_t LF = h->md.in_dim;
   const Prec gp = h->prec == Prec::F64 ? Prec::F64 : Prec::F32;
+  // grouped lanes: the x neighbours' and features' adds of a corner pair leave as
+  // one atomic request (2^16 points, 16 levels of 2^17 entries: 840 -> 263 us;
+  // the level mapping makes no difference, the request rate is the bound).
+  // fp64 has the one-thread-per-sample form only.
   HIPCHK(launch_scatter(gp, h->ld, 0, h->enc.n_levels, nullptr, nullptr, (int)n, 0, nullptr, coords, dfeats, LF,
-                        h->enc.n_features, dtable,
-                        0, 0, 0, (hipStream_t)stream));
+                        h->enc.n_features, dtable, gp == Prec::F32 ? 1 : 0, 0, 0, (hipStream_t)stream));
   return DVNR_OK;
 }
 

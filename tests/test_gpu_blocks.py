@@ -8,10 +8,11 @@ four layers, a normwise error of a few 1e-6 at most; the bar is the 1e-5 that
 the other fp32 results are held to.  A unit within fp32 rounding of its ReLU
 kink may fall on either side, so dL/do is zero for samples that have one.
 """
+import numpy as np
 import pytest
 import torch
 
-from tests.test_gpu_parity import make, normwise
+from tests.test_gpu_parity import dev, make, normwise
 from oracle import dvnr_oracle as o
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +55,23 @@ def test_mlp_blocks_fp32(levels, features, hidden, width):
         assert normwise(out.cpu(), ref.detach().cpu()) < 1e-5
         assert normwise(dx.cpu(), grads[0].cpu()) < 1e-5
         assert normwise((dw.double() - 0.5).cpu(), ref_dw.cpu()) < 1e-5 + 2e-7 / float(ref_dw.abs().max())
+
+
+@pytest.mark.parametrize("levels,features", [(16, 2), (9, 1), (8, 4), (4, 8), (3, 1)])
+def test_encode_blocks_fp32(levels, features):
+    """Encoding forward and backward over sample counts at the edges of a
+    256-sample tile, for both level mappings (more than 8 levels, and fewer)."""
+    enc = o.Encoding(levels, features, 10, 4, 1.25)
+    lay = o.layout(enc, o.MLP(1, 16))
+    model = make((enc, o.MLP(1, 16)), [((8, 8, 8), 0)])
+    rng = np.random.default_rng(levels)
+    for n in (1, 255, 257, 1000):
+        print(f"[blocks] encode {levels}x{features} n={n}", flush=True)
+        x = rng.random((n, 3)).astype(np.float32)
+        table = rng.uniform(-1, 1, lay.n_table_params).astype(np.float32)
+        dy = rng.uniform(-1, 1, (n, levels * features)).astype(np.float32)
+        g = torch.zeros(lay.n_table_params, device="cuda")
+        feats = model.encode_forward(dev(x), dev(table))
+        model.encode_backward(dev(x), dev(dy), g)
+        assert normwise(feats.cpu(), o.encode(lay, table.astype(np.float64), x)) < 1e-5
+        assert normwise(g.cpu(), o.encode_backward(lay, x, dy.astype(np.float64))) < 1e-5
