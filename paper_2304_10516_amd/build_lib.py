@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdvnr.so")
-SOURCES = ["dvnr_host.hip", "k_core.hip", "k_mlp.hip", "k_mlp_blocks.hip", "k_sort.hip", "k_decode.hip", "k_render.hip",
+SOURCES = ["dvnr_host.hip", "k_core.hip", "k_mlp.hip", "k_mlp_blocks.hip", "k_sort.hip", "k_decode.hip",
+           "k_decode_w16.hip", "k_decode_w32.hip", "k_decode_w64.hip", "k_render.hip",
            "k_encode_bin.hip", "k_scatter_part.hip", "micro.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -252,13 +252,12 @@ hipError_t launch_mlp_simple_bwd(const MlpDesc& md, int64_t n, const double* fea
                                  const double* dout, double* dfeats, double* dw, hipStream_t s);
 
 // Fused decode of one block (voxel centers, encoding through LDS-staged vertex
-// boxes, MLP forward); table / wsrc point at element 0 of the parameter index
-// space (fp16 / bf16 working copy for mixed precision, fp32 masters otherwise).
+// boxes, MLP forward); table points at element 0 of the parameter index space
+// and wsrc at the first weight of block 0 (fp16 / bf16 working copy for mixed
+// precision, fp32 masters otherwise).
 hipError_t launch_decode_fused(Prec p, const LevelDesc& ld, const MlpDesc& md, const BlockMeta* meta,
                                const BlockRange* range, int block, const int32_t* dims, const void* table,
-                               const void* wsrc, int64_t n_table_params, void* opnd, float* out, hipStream_t s);
-// Device scratch of the fused decode: the block's MLP operands in operand order.
-constexpr int kDecOperandBytes = 1 << 16;
+                               const void* wsrc, float* out, hipStream_t s);
 
 // Direct volume rendering by sample streaming (one block's unit cube).
 struct RayCamera {
