@@ -19,8 +19,7 @@
  *    (allocated by the caller, e.g. with torch); "host" pointers are ordinary
  *    host memory.  The library allocates no device memory of its own: the
  *    caller sizes the buffers with dvnr_get_sizes() and hands them over with
- *    dvnr_bind().  Device buffers must be 256-byte aligned.  The one device
- *    array the library holds is the static scratch of dvnr_render_static.
+ *    dvnr_bind().  Device buffers must be 256-byte aligned.
  *  - Every entry point that launches work takes a hipStream_t (passed as
  *    void*; NULL = the default stream) and only enqueues; no entry point
  *    synchronizes except dvnr_sync() and dvnr_mse_fp64() (which returns a host
@@ -244,17 +243,19 @@ dvnr_status dvnr_decode(dvnr_t* h, int32_t block, float* out, void* stream);
  * alpha = 1 - (1 - a)^(step / ref_step); then C += (1 - A) alpha rgb and
  * A += (1 - A) alpha.  A ray stops after the sample that brings A to
  * alpha_stop or above (1 disables early termination).
- * Rays advance samples_per_round samples per round: coordinate generation,
- * INR inference over the batch, shading (chunks of max_batch samples).
+ * The rays of neighbouring pixels are marched together by one kernel that
+ * evaluates the INR and composites; a ray counts as active in a round of
+ * samples_per_round samples when it enters the round (samples_out below).
  * Camera: pixel (i, j), row 0 at the top, looks along
  * normalize(f + px r + py u) with f = normalize(center - eye),
  * r = normalize(f x up), u = r x f, px = (2 (i + 1/2) / width - 1) tan(fovy/2)
  * width / height, py = (1 - 2 (j + 1/2) / height) tan(fovy/2), all in float32
  * round-to-nearest in that order (the sample count of a ray is decided by
  * them).  image: device float [height][width][4], premultiplied (C, A).
- * workspace: device, 256-byte aligned, dvnr_render_workspace_bytes bytes.
- * samples_out (host, may be NULL): samples generated and inferred, the
- * rounds' active rays times samples_per_round.  Synchronizes `stream`. */
+ * workspace: device, 256-byte aligned, dvnr_render_workspace_bytes bytes (a
+ * ray's state is kept in registers; its contents are left alone).
+ * samples_out (host, may be NULL): the rounds' active rays times
+ * samples_per_round.  Synchronizes `stream`. */
 typedef struct dvnr_camera {
   float eye[3], center[3], up[3];
   float fovy_deg;        /* (0, 180) */
@@ -274,20 +275,12 @@ dvnr_status dvnr_render_workspace_bytes(const dvnr_t* h, int32_t width, int32_t 
 dvnr_status dvnr_render(dvnr_t* h, int32_t block, const dvnr_camera* cam, const dvnr_render_params* params,
                         const float* tf, void* workspace, float* image, int64_t* samples_out, void* stream);
 
-/* dvnr_render for callers that cannot allocate device memory (code under
- * stream or graph capture, serving loops, harnesses that forbid hipMalloc):
- * the same renderer and the same image, but the per-ray state (the
- * `workspace` of dvnr_render) lives in one static device array of the library,
- * one copy per GPU, sized for at most DVNR_RENDER_STATIC_MAX_RAYS pixels
- * (width * height; 28 MiB of device memory per GPU the library runs on, held
- * until the process ends).  Larger images: DVNR_E_INVALID, nothing enqueued.
- * Calls no allocator.  The first call on a device looks up that device's copy
- * (the current device) and may return DVNR_E_HIP if that fails.  Every call on
- * one GPU, from any handle or thread, shares that GPU's array and the array
- * keeps the last call's contents; calls that overlap on one GPU (different
- * streams or threads) race and must be serialized by the caller.  The
- * handle's own bound workspace carries the sample batches, as in
- * dvnr_render.  Synchronizes `stream`. */
+/* dvnr_render for callers without a workspace (serving loops, harnesses that
+ * forbid hipMalloc): the same renderer and the same image, for at most
+ * DVNR_RENDER_STATIC_MAX_RAYS pixels (width * height).  Larger images:
+ * DVNR_E_INVALID, nothing enqueued.  Calls no allocator; the handle's bound
+ * workspace carries the round counters, as in dvnr_render.  Synchronizes
+ * `stream`. */
 #define DVNR_RENDER_STATIC_MAX_RAYS (1 << 20)
 dvnr_status dvnr_render_static(dvnr_t* h, int32_t block, const dvnr_camera* cam, const dvnr_render_params* params,
                                const float* tf, float* image, int64_t* samples_out, void* stream);

@@ -10,9 +10,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdvnr.so")
-SOURCES = ["dvnr_host.hip", "k_core.hip", "k_mlp.hip", "k_mlp_blocks.hip", "k_sort.hip", "k_decode.hip",
-           "k_decode_w16.hip", "k_decode_w32.hip", "k_decode_w64.hip", "k_render.hip",
-           "k_encode_bin.hip", "k_scatter_part.hip", "micro.hip"]
+WIDTHS = (16, 32, 64)  # networks' widths, a translation unit each
+SOURCES = [f"k_{part}_w{w}.hip" for w in WIDTHS for part in ("render", "query", "decode")] + [
+    "dvnr_host.hip", "k_core.hip", "k_mlp.hip", "k_mlp_blocks.hip", "k_sort.hip", "k_infer.hip", "k_encode_bin.hip",
+    "k_scatter_part.hip", "micro.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -9,7 +9,8 @@
 // segments on hashed ones, whose x prime is 1), then every voxel interpolates
 // its 8 corners from LDS: ~9 global loads per voxel instead of 128 gathers.
 // A level whose box is larger than the direct gathers would be, or that no
-// longer fits the LDS left, gathers directly.
+// longer fits the LDS left, gathers directly, all lanes of a wave on one such
+// level at a time.
 //
 // Lane (g, c) of a wave interpolates, for voxel column c, the levels whose
 // features the MFMA forward wants from lane group g (features 8 g .. 8 g + 7,
@@ -24,13 +25,13 @@
 //
 // The kernel is bound by VALU issue (a SIMD issues one wave instruction in
 // four cycles; 90 % busy by the counters on the 256^3 grid of the 16-level,
-// 2 x 64 model in mixed precision): 1,402 VALU instructions per wave of 64
+// 2 x 64 model in mixed precision): 1,425 VALU instructions per wave of 64
 // voxels, of which about 620 interpolate, 340 fill the boxes and 350 run the
 // network.  With the boxes filled by every wave one level after the other (a
 // barrier pair per level), a voxel's levels all in one lane, the features
 // staged in LDS and the operands arranged by a kernel of its own it was 2,343:
-// 0.96 -> 0.68 ms (24.6 G voxels/s), 64 uneven blocks 9.87 -> 7.65 ms, a
-// 67x61x50 grid of the 4-level 1 x 16 fp32 model 21 -> 14 us.
+// 0.96 -> 0.68 ms (24.8 G voxels/s), 64 uneven blocks 9.87 -> 7.76 ms, a
+// 67x61x50 grid of the 4-level 1 x 16 fp32 model 21 -> 13 us.
 #pragma once
 
 #include <algorithm>
@@ -48,6 +49,7 @@ constexpr int kBoxMaxVerts = 2048;          // a larger box costs more than the 
 // of 3 take 7.76 ms, of 1 7.65 ms).
 constexpr int kDecodeRun = 8;               // at most
 constexpr int kDecodeGrid = 8192;           // workgroups to keep: eight rounds of four per CU
+constexpr int kOneWaveVerts = 512;          // (256: the 256^3 decode 0.71 instead of 0.68 ms)
 constexpr int kDecodeLdsBytes = 40 * 1024;  // most LDS for boxes (three workgroups per CU and more)
 
 template <typename TT> __device__ __forceinline__ float tload(const TT* p) { return (float)*p; }
@@ -65,6 +67,19 @@ struct BrickLevel {
   int lo[3];     // box origin
 };
 typedef const __attribute__((address_space(3))) unsigned char lds_byte;
+
+// The words of a table entry of VB bytes, read with the widest access that its
+// alignment (VB, at most 16 bytes) allows.
+typedef uint32_t u32x2d __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4d __attribute__((ext_vector_type(4)));
+template <int VB>
+struct EntryWords {
+  typedef typename std::conditional<
+      VB == 2, uint16_t,
+      typename std::conditional<VB == 4, uint32_t, typename std::conditional<VB == 8, u32x2d, u32x4d>::type>::type>::type
+      word;
+  static constexpr int N = VB / (int)sizeof(word);
+};
 
 // Brick counts of a block and the factors that divide by them: for a < 2^31,
 // a / d = umulhi(a, m) >> sh with the m and sh below (Granlund and Montgomery:
@@ -100,9 +115,13 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
   constexpr int LPG = 8 / F;        // levels of a lane
   constexpr int SETS = 4 / NG;      // lane-group sets, each with z of its own
   constexpr int VB = F * (int)sizeof(TT);
+  typedef typename EntryWords<VB>::word word;
+  constexpr int NW = EntryWords<VB>::N;
   extern __shared__ __align__(16) unsigned char dsm[];
   TT* box = reinterpret_cast<TT*>(dsm);
   __shared__ BrickLevel lev[kMaxLevels];
+  __shared__ unsigned large_boxes;  // levels (bits) whose boxes the waves fill together
+  __shared__ unsigned no_boxes;     // levels (bits) that gather from the table
   __shared__ __align__(16) typename M::op_t opnd[M::N_SLOTS * 64];
   __shared__ __align__(16) float wout[W];
 
@@ -160,8 +179,14 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
         const int p = __shfl_up(end, o, 64);
         if (lane >= o) end += p;
       }
+      const bool boxed = lane < ld.L && small && end <= box_entries;
+      const unsigned long long lg = __ballot(boxed && nv > kOneWaveVerts);
+      const unsigned long long nb = __ballot(lane < ld.L && !boxed);
+      if (lane == 0) {
+        large_boxes = (unsigned)lg;
+        no_boxes = (unsigned)nb;
+      }
       if (lane < ld.L) {
-        const bool boxed = small && end <= box_entries;
         const int start = end - nv;
         BrickLevel b;
         b.scale = sc;
@@ -183,13 +208,14 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
     }
     __syncthreads();
 
-    // ---- fill the boxes: wave w takes levels w, 7 - w, 8 + w, 15 - w (coarse and
-    // fine ones mixed)
-    for (int p = 0; p < (ld.L + 3) / 4; ++p) {
-      const int l = 4 * p + ((p & 1) ? 3 - wave : wave);
-      if (l >= ld.L) continue;
+    // ---- fill the boxes.  Up to kOneWaveVerts vertices are one wave's work: wave w
+    // takes levels w, 7 - w, 8 + w, 15 - w (coarse and fine ones mixed); the
+    // waves share larger boxes.
+    const unsigned large = __builtin_amdgcn_readfirstlane(large_boxes);
+    const unsigned no_box = __builtin_amdgcn_readfirstlane(no_boxes);
+    auto fill_box = [&](int l, bool shared) {
       const int nv = __builtin_amdgcn_readfirstlane(lev[l].nv);
-      if (nv == 0) continue;
+      if (nv == 0) return;
       const int dx = __builtin_amdgcn_readfirstlane(lev[l].dx), dy = __builtin_amdgcn_readfirstlane(lev[l].dy);
       const int lo0 = __builtin_amdgcn_readfirstlane(lev[l].lo[0]);
       const int lo1 = __builtin_amdgcn_readfirstlane(lev[l].lo[1]);
@@ -224,51 +250,42 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
         }
         // all loads in flight together (the last vertex stands in past the box's
         // end), then the stores
-        if constexpr (VB % 4 == 0) {
-          constexpr int NW = VB / 4;
-          const uint32_t* tw = reinterpret_cast<const uint32_t*>(tab);
-          uint32_t* bw = reinterpret_cast<uint32_t*>(box);
-          uint32_t r[UN][NW];
+        const word* tw = reinterpret_cast<const word*>(tab);
+        word* bw = reinterpret_cast<word*>(box);
+        word r[UN][NW];
 #pragma unroll
-          for (int u = 0; u < UN; ++u)
+        for (int u = 0; u < UN; ++u)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) r[u][w] = tw[e[u] * (uint32_t)NW + w];
+          for (int w = 0; w < NW; ++w) r[u][w] = tw[e[u] * (uint32_t)NW + w];
 #pragma unroll
-          for (int u = 0; u < UN; ++u) {
-            const int v = v0 + 64 * u + lane;
-            if (v < nv)
+        for (int u = 0; u < UN; ++u) {
+          const int v = v0 + 64 * u + lane;
+          if (v < nv)
 #pragma unroll
-              for (int w = 0; w < NW; ++w) bw[(start + v) * NW + w] = r[u][w];
-          }
-        } else {
-          TT r[UN][F];
-#pragma unroll
-          for (int u = 0; u < UN; ++u)
-#pragma unroll
-            for (int f = 0; f < F; ++f) r[u][f] = tab[e[u] * (uint32_t)F + f];
-#pragma unroll
-          for (int u = 0; u < UN; ++u) {
-            const int v = v0 + 64 * u + lane;
-            if (v < nv)
-#pragma unroll
-              for (int f = 0; f < F; ++f) box[(start + v) * F + f] = r[u][f];
-          }
+            for (int w = 0; w < NW; ++w) bw[(start + v) * NW + w] = r[u][w];
         }
       };
       auto fill_level = [&](auto dense_tag) {
-        int v0 = 0;
-        for (; nv - v0 > 128; v0 += 256) fill(std::integral_constant<int, 4>{}, v0, dense_tag);
-        if (nv - v0 > 64) {
-          fill(std::integral_constant<int, 2>{}, v0, dense_tag);
-        } else if (nv > v0) {
-          fill(std::integral_constant<int, 1>{}, v0, dense_tag);
+        if (shared) {
+          for (int v0 = 128 * wave; v0 < nv; v0 += 512) fill(std::integral_constant<int, 2>{}, v0, dense_tag);
+        } else if (nv > 128) {
+          for (int v0 = 0; v0 < nv; v0 += 256) fill(std::integral_constant<int, 4>{}, v0, dense_tag);
+        } else if (nv > 64) {
+          fill(std::integral_constant<int, 2>{}, 0, dense_tag);
+        } else {
+          fill(std::integral_constant<int, 1>{}, 0, dense_tag);
         }
       };
       if (ld.dense[l])
         fill_level(std::true_type{});
       else
         fill_level(std::false_type{});
+    };
+    for (int p = 0; p < (ld.L + 3) / 4; ++p) {
+      const int l = 4 * p + ((p & 1) ? 3 - wave : wave);
+      if (l < ld.L && !((large >> l) & 1)) fill_box(l, false);
     }
+    for (unsigned m = large; m != 0; m &= m - 1) fill_box(__builtin_ctz(m), true);
     __syncthreads();
     if (y0 + wave < ny) {  // (uniform over the wave)
       // ---- interpolation: lane (g, c), z = z0 + set + SETS t for t < NG
@@ -282,6 +299,8 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
       for (int j = 0; j < LPG; ++j) {
         const int l = LPG * fg + j;
         const bool live = l < ld.L;
+        const uint32_t keep = live ? ~0u : 0u;
+        if (j > 0) __builtin_amdgcn_sched_barrier(0);
         const BrickLevel& b = lev[live ? l : 0];
         const float sc = b.scale;
         const int R = b.R, sy = b.sy, sz = b.sz;
@@ -293,23 +312,23 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
 #pragma unroll
         for (int k = 0; k < 4; ++k) wxy[k] = ((k & 1) ? tx : 1.0f - tx) * ((k & 2) ? ty : 1.0f - ty);
         float acc[NG][F];
+#pragma unroll
+        for (int t = 0; t < NG; ++t)
+#pragma unroll
+          for (int f = 0; f < F; ++f) acc[t][f] = 0.0f;
         if (sy != 0) {
           const uint32_t b0 = b.base + (uint32_t)(VB * ix) + (uint32_t)__mul24(sy, iy);
 #pragma unroll
           for (int t = 0; t < NG; ++t) {
+            if (F >= 4 && t > 0) __builtin_amdgcn_sched_barrier(0);
             int iz;
             float tz;
             center_pos(pz[t], sc, R, iz, tz);
             const uint32_t v0 = b0 + (uint32_t)__mul24(sz, iz);
 #pragma unroll
-            for (int f = 0; f < F; ++f) acc[t][f] = 0.0f;
-#pragma unroll
             for (int k = 0; k < 8; ++k) {
               const float w = wxy[k & 3] * ((k & 4) ? tz : 1.0f - tz);
-              // read as words where an entry is whole words (the box is word-aligned)
-              typedef typename std::conditional<VB % 4 == 0, uint32_t, uint16_t>::type word;
               typedef const __attribute__((address_space(3))) word lds_word;
-              constexpr int NW = VB / (int)sizeof(word);
               lds_word* v = (lds_word*)(uintptr_t)(v0 + ((k & 2) ? sy : 0) + ((k & 4) ? sz : 0)) + (k & 1) * NW;
               word e[NW];
 #pragma unroll
@@ -320,32 +339,12 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
               for (int f = 0; f < F; ++f) acc[t][f] += w * tload(&ev[f]);
             }
           }
-        } else {
-          const int lc = live ? l : 0;
-          const TT* tab = tab0 + (int64_t)ld.off[lc] * F;
-          const int dense = ld.dense[lc];
-#pragma unroll
-          for (int t = 0; t < NG; ++t) {
-            int iz;
-            float tz;
-            center_pos(pz[t], sc, R, iz, tz);
-#pragma unroll
-            for (int f = 0; f < F; ++f) acc[t][f] = 0.0f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-              const float w = wxy[k & 3] * ((k & 4) ? tz : 1.0f - tz);
-              const uint32_t e =
-                  corner_index(dense, R, ld.T_mask, ix + (k & 1), iy + ((k >> 1) & 1), iz + (k >> 2));
-#pragma unroll
-              for (int f = 0; f < F; ++f) acc[t][f] += w * tload(tab + (int64_t)e * F + f);
-            }
-          }
         }
 #pragma unroll
         for (int t = 0; t < NG; ++t)
 #pragma unroll
           for (int f = 0; f < F; ++f) {
-            const float v = live ? acc[t][f] : 0.0f;
+            const float v = __uint_as_float(__float_as_uint(acc[t][f]) & keep);
             if constexpr (BF16)
               xb[t][0][j * F + f] = (__bf16)v;
             else
@@ -353,31 +352,55 @@ __global__ __launch_bounds__(256, BF16 ? 4 : 2) void k_decode_fused(
           }
       }
 
-      // ---- MLP forward of the four z, each with its own lane groups' features
-      f32x4i wo[M::MT];
+      // ---- levels without a box, one after the other: lane (g, c) gathers for
+      // the voxel z = z0 + g (all lanes at work), and the lane groups that the
+      // level's features belong to fetch them
+      if (no_box != 0) {
+        const float zg = __shfl(rowz, g, 64);
+        for (unsigned m = no_box; m != 0; m &= m - 1) {
+          const int l = __builtin_ctz(m), R = ld.R[l], dense = ld.dense[l];
+          const float sc = ld.scale[l];
+          const TT* tab = tab0 + (int64_t)ld.off[l] * F;
+          int ix, iy, iz;
+          float tx, ty, tz;
+          center_pos(px, sc, R, ix, tx);
+          center_pos(py, sc, R, iy, ty);
+          center_pos(zg, sc, R, iz, tz);
+          float acc[F];
 #pragma unroll
-      for (int m = 0; m < M::MT; ++m) wo[m] = *reinterpret_cast<const f32x4i*>(&wout[16 * m + 4 * g]);
-      float o = 0.0f;
+          for (int f = 0; f < F; ++f) acc[f] = 0.0f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        typename M::op_t xq[M::KS_IN];
+          for (int k = 0; k < 8; ++k) {
+            const float w = ((k & 1) ? tx : 1.0f - tx) * ((k & 2) ? ty : 1.0f - ty) * ((k & 4) ? tz : 1.0f - tz);
+            const uint32_t e = corner_index(dense, R, ld.T_mask, ix + (k & 1), iy + ((k >> 1) & 1), iz + (k >> 2));
+            word ew[NW];
 #pragma unroll
-        for (int s = 0; s < M::KS_IN; ++s) {
-          xq[s] = xb[q / SETS][s];
-          if constexpr (SETS > 1) {
-            if (set != q % SETS) {
-              if constexpr (BF16) {
+            for (int i = 0; i < NW; ++i) ew[i] = reinterpret_cast<const word*>(tab)[e * (uint32_t)NW + i];
+            TT ev[F];
+            __builtin_memcpy(ev, ew, VB);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) xq[s][j] = (__bf16)0.0f;
-              } else {
-                xq[s] = 0.0f;
-              }
-            }
+            for (int f = 0; f < F; ++f) acc[f] += w * tload(&ev[f]);
           }
+          const int owner = l / LPG, at = l % LPG;
+#pragma unroll
+          for (int t = 0; t < NG; ++t)
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+              const float v = __shfl(acc[f], 16 * (set + SETS * t) + c, 64);
+#pragma unroll
+              for (int j = 0; j < LPG; ++j)
+                if (j == at && fg == owner) {
+                  if constexpr (BF16)
+                    xb[t][0][j * F + f] = (__bf16)v;
+                  else
+                    xb[t][j * F + f] = v;
+                }
+            }
         }
-        const float v = M::eval(opnd, wo, lane, xq);
-        if (g == q) o = v;
       }
+
+      // ---- MLP forward of the four z
+      const float o = M::template eval_groups<4, NG>(opnd, wout, lane, xb);
       // lane group g stores z = z0 + g
       if (x0 + c < nx && z0 + g < nz)
         out[((int64_t)(z0 + g) * ny + (y0 + wave)) * nx + x0 + c] = o * br.range + br.vmin;

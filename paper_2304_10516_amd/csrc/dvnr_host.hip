@@ -5,7 +5,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -1282,19 +1281,41 @@ static ModelSrc live_src(const dvnr_t* h) {
   return ModelSrc{h->prec == Prec::MIXED ? (const void*)h->buf.work16 : (const void*)h->buf.params, h->d_range()};
 }
 
+// Whether n coordinates go through the one-kernel query (k_query) or through
+// the tile encoding and the network in two passes.  The query saves a launch
+// and the features' way through memory, but its gathers touch every level at
+// once where the tile encoding gives each XCD two levels, whose tables fit its
+// L2.  Measured (2 x 64, uniformly random points, us):
+//   16 levels, F 2, 17.8 MB fp16: 2^12 points 10 against 12, 2^14 14 / 13,
+//     2^20 527 / 328; 36 MB fp32: 2^20 660 / 530
+//   16 levels, F 2, 1.7 MB fp16: 2^16 23 / 25, 2^20 325 / 317; 3.5 MB fp32:
+//     2^20 374 / 471
+//   8 levels, F 4, 18 MB fp16: 2^20 307 / 237; 1.7 MB: 179 / 194; 36 MB fp32: 434 / 548
+//   4 levels, F 8, 18 MB fp16: 2^20 183 / 209; 35 MB fp32: 295 / 436
+static bool query_in_one_kernel(const dvnr_t* h, int64_t n) {
+  constexpr int64_t kFew = 1 << 13, kMedium = 1 << 17, kL2Bytes = (int64_t)4 << 20;  // of one XCD
+  const bool mixed = h->prec == Prec::MIXED;
+  const int L = h->enc.n_levels;
+  if (std::min(n, h->max_batch) <= kFew) return true;
+  if (L <= (mixed ? 4 : 8)) return true;
+  return h->n_table * (int64_t)h->ielem() <= kL2Bytes && (!mixed || L <= 8 || n <= kMedium);
+}
+
 static dvnr_status infer_coords(dvnr_t* h, int b, int64_t n, const float* coords, float* out, hipStream_t s,
                                 const ModelSrc& src) {
   const bool mixed = h->prec == Prec::MIXED;
   const int64_t F = h->enc.n_features;
-  const void* table = src.params;
-  const void* wsrc = mixed ? (const void*)((const uint16_t*)src.params + h->n_table)
-                           : (const void*)((const float*)src.params + h->n_table);
+  const void* wsrc = (const char*)src.params + h->n_table * (int64_t)h->ielem();
+  if (query_in_one_kernel(h, n)) {
+    HIPCHK(launch_query(h->prec, h->ld, h->md, h->d_meta(), src.range, b, src.params, wsrc, n, coords, out, s));
+    return DVNR_OK;
+  }
   for (int64_t c0 = 0; c0 < n; c0 += h->max_batch) {
     const int64_t cn = std::min(h->max_batch, n - c0);
     HIPCHK(launch_encode(h->prec, mixed ? 1 : 0, h->ld, h->d_meta(), nullptr, (int)cn, b, nullptr, coords + 3 * c0,
-                         table, h->d_feat(), F, h->max_batch * F, h->xcd_map, s));
-    HIPCHK(launch_mlp_infer(h->prec, h->md, h->ld, h->d_meta(), src.range, nullptr, nullptr, (int)cn, b,
-                            h->d_feat(), wsrc, h->max_batch, out + c0, s));
+                         src.params, h->d_feat(), F, h->max_batch * F, h->xcd_map, s));
+    HIPCHK(launch_mlp_infer(h->prec, h->ld, h->md, h->d_meta(), src.range, b, wsrc, (int)cn, h->d_feat(),
+                            h->max_batch, out + c0, s));
   }
   return DVNR_OK;
 }
@@ -1346,10 +1367,11 @@ dvnr_status dvnr_decode(dvnr_t* h, int32_t block, float* out, void* stream) {
 }
 
 // ---------------------------------------------------------------------------
-// Direct volume rendering (sample streaming)
+// Direct volume rendering
 // ---------------------------------------------------------------------------
 static constexpr int64_t render_ws_bytes(int64_t n) {
-  // directions [n][3], (t0, t1) [n][2], two active-ray lists [n], two counters
+  // part of the interface: room for a ray's state per pixel (the renderer keeps
+  // it in registers)
   return align256(12 * n) + align256(8 * n) + 2 * align256(4 * n) + 256;
 }
 
@@ -1376,20 +1398,11 @@ static dvnr_status render_args(dvnr_t* h, int32_t block, const dvnr_camera* cam,
   return DVNR_OK;
 }
 
-// The renderer proper on a checked argument set; `workspace` holds
-// render_ws_bytes(width * height) bytes, 256-byte aligned.
+// The renderer proper on a checked argument set.
 static dvnr_status render_impl(dvnr_t* h, int32_t block, const dvnr_camera* cam, const dvnr_render_params* rp,
-                               const float* tf, void* workspace, float* image, int64_t* samples_out, void* stream) {
+                               const float* tf, float* image, int64_t* samples_out, void* stream) {
   try {
-    dvnr_status st = DVNR_OK;
     hipStream_t s = (hipStream_t)stream;
-    const int64_t n = (int64_t)cam->width * cam->height;
-    char* ws = (char*)workspace;
-    float* dirs = (float*)ws;
-    float* t01 = (float*)(ws + align256(12 * n));
-    int32_t* list[2] = {(int32_t*)(ws + align256(12 * n) + align256(8 * n)),
-                        (int32_t*)(ws + align256(12 * n) + align256(8 * n) + align256(4 * n))};
-    int32_t* counters = (int32_t*)(ws + align256(12 * n) + align256(8 * n) + 2 * align256(4 * n));
     RayCamera rc;
     for (int a = 0; a < 3; ++a) {
       rc.eye[a] = cam->eye[a];
@@ -1397,35 +1410,35 @@ static dvnr_status render_impl(dvnr_t* h, int32_t block, const dvnr_camera* cam,
       rc.up[a] = cam->up[a];
     }
     rc.tan_h = (float)std::tan((double)cam->fovy_deg * 3.14159265358979323846 / 360.0);
-    const int S = rp->samples_per_round;
-    const float opacity_exp = (float)((double)rp->step / (double)rp->ref_step);
-    const float tf_inv = (float)(1.0 / ((double)rp->tf_hi - (double)rp->tf_lo));
+    RenderStep rs;
+    rs.dt = rp->step;
+    rs.opacity_exp = (float)((double)rp->step / (double)rp->ref_step);
+    rs.alpha_stop = rp->alpha_stop;
+    rs.tf_lo = rp->tf_lo;
+    rs.tf_inv_range = (float)(1.0 / ((double)rp->tf_hi - (double)rp->tf_lo));
+    rs.n_tf = rp->n_tf;
+    rs.S = rp->samples_per_round;
     const ModelSrc src = live_src(h);
-    HIPCHK(launch_zero(counters, 2 * sizeof(int32_t), s));
-    HIPCHK(launch_ray_init(rc, cam->width, cam->height, dirs, t01, image, list[0], counters, s));
-    int32_t n_active = 0;
-    HIPCHK(hipMemcpyAsync(&n_active, counters, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    const void* wsrc = (const char*)src.params + h->n_table * (int64_t)h->ielem();
+    // a ray crosses the unit cube in at most sqrt(3) / step samples; one launch
+    // takes as many of them as keep it short (2^31 samples over the image), the
+    // next one goes on from the image
+    const int64_t pixels = (int64_t)cam->width * cam->height;
+    const int64_t k_max = (int64_t)std::min(1.7330 / (double)rp->step + 8.0, 2147483000.0);
+    const int64_t per = std::min<int64_t>(4096, std::max<int64_t>(64, ((int64_t)1 << 31) / pixels / 16 * 16));
+    unsigned long long* rounds = (unsigned long long*)h->d_coords();  // per-step scratch, at least 3 KB
+    static_assert(kRenderSlots * 64 <= 3 * 4 * 256, "the counters fit the coordinates of the smallest max_batch");
+    HIPCHK(launch_zero(rounds, kRenderSlots * 64, s));
+    for (int64_t k0 = 0; k0 < k_max; k0 += per)
+      HIPCHK(launch_render(h->prec, h->ld, h->md, h->d_meta(), src.range, block, src.params, wsrc, rc, cam->width,
+                           cam->height, rs, (int)k0, (int)std::min(k0 + per, (k_max + 15) / 16 * 16), tf, image, rounds,
+                           s));
+    unsigned long long cnt[kRenderSlots * 8];
+    HIPCHK(hipMemcpyAsync(cnt, rounds, sizeof(cnt), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    const int chunk = std::max<int64_t>(1, h->max_batch / S);
-    int cur = 0;
-    int64_t generated = 0;
-    for (int k_base = 0; n_active > 0; k_base += S) {
-      HIPCHK(launch_zero(counters + 1, sizeof(int32_t), s));
-      generated += (int64_t)n_active * S;
-      for (int c0 = 0; c0 < n_active; c0 += chunk) {
-        const int cn = std::min(chunk, n_active - c0);
-        HIPCHK(launch_ray_gen(rc, list[cur] + c0, cn, k_base, S, rp->step, dirs, t01, h->d_coords(), s));
-        st = infer_coords(h, block, (int64_t)cn * S, h->d_coords(), h->d_target(), s, src);
-        if (st) return st;
-        HIPCHK(launch_ray_shade(list[cur] + c0, cn, k_base, S, rp->step, opacity_exp, rp->alpha_stop, t01,
-                                h->d_target(), tf, rp->n_tf, rp->tf_lo, tf_inv, image, list[1 - cur], counters + 1,
-                                s));
-      }
-      HIPCHK(hipMemcpyAsync(&n_active, counters + 1, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
-      cur = 1 - cur;
-    }
-    if (samples_out) *samples_out = generated;
+    int64_t total = 0;
+    for (int i = 0; i < kRenderSlots; ++i) total += (int64_t)cnt[8 * i];
+    if (samples_out) *samples_out = total * rs.S;
     return DVNR_OK;
   } catch (...) {
     return fail(DVNR_E_INVALID, "render failed");
@@ -1438,35 +1451,7 @@ dvnr_status dvnr_render(dvnr_t* h, int32_t block, const dvnr_camera* cam, const 
   if (st) return st;
   if (!workspace) return fail(DVNR_E_INVALID, "null workspace");
   if (((uintptr_t)workspace) % 256) return fail(DVNR_E_INVALID, "workspace must be 256-byte aligned");
-  return render_impl(h, block, cam, rp, tf, workspace, image, samples_out, stream);
-}
-
-// ---------------------------------------------------------------------------
-// Rendering without a caller workspace: the ray state lives in one static
-// device array per GPU.  Host code never passes `scratch` itself to a kernel
-// (on the host its name is only a stand-in for the symbol): its device address
-// is looked up once per device and used instead.
-// ---------------------------------------------------------------------------
-static constexpr int64_t kRenderStaticBytes = render_ws_bytes(DVNR_RENDER_STATIC_MAX_RAYS);  // 28 MiB + 256 B
-static __device__ __align__(256) char scratch[kRenderStaticBytes];
-
-static std::mutex g_scratch_mu;
-static std::vector<void*> g_scratch_ptr;  // per device ordinal; nullptr until looked up
-
-// Device address of this GPU's `scratch` (the current device's copy).
-static dvnr_status static_scratch(void** out) {
-  int dev = -1;
-  HIPCHK(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if ((int)g_scratch_ptr.size() <= dev) g_scratch_ptr.resize(dev + 1, nullptr);
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    HIPCHK(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
-    if (!p || ((uintptr_t)p) % 256) return fail(DVNR_E_HIP, "static render scratch has no aligned device address");
-    g_scratch_ptr[dev] = p;
-  }
-  *out = g_scratch_ptr[dev];
-  return DVNR_OK;
+  return render_impl(h, block, cam, rp, tf, image, samples_out, stream);
 }
 
 dvnr_status dvnr_render_static(dvnr_t* h, int32_t block, const dvnr_camera* cam, const dvnr_render_params* rp,
@@ -1475,10 +1460,7 @@ dvnr_status dvnr_render_static(dvnr_t* h, int32_t block, const dvnr_camera* cam,
   if (st) return st;
   if ((int64_t)cam->width * cam->height > DVNR_RENDER_STATIC_MAX_RAYS)
     return fail(DVNR_E_INVALID, "dvnr_render_static: image larger than DVNR_RENDER_STATIC_MAX_RAYS pixels");
-  void* ws = nullptr;
-  st = static_scratch(&ws);
-  if (st) return st;
-  return render_impl(h, block, cam, rp, tf, ws, image, samples_out, stream);
+  return render_impl(h, block, cam, rp, tf, image, samples_out, stream);
 }
 
 // ---------------------------------------------------------------------------

@@ -219,11 +219,11 @@ hipError_t launch_mlp_train(Prec p, const MlpDesc& md, const LevelDesc& ld, cons
                             const float* target, const void* weights_src, float* dfeat, int64_t plane,
                             float* slots, int64_t slot_stride, int grid, int loss_l1, int min_waves, int wg_waves,
                             hipStream_t s);
-// MLP inference: out[i] = INR output de-normalized with the block range.
-hipError_t launch_mlp_infer(Prec p, const MlpDesc& md, const LevelDesc& ld, const BlockMeta* meta,
-                            const BlockRange* range, const BlockPlan* plan, const Tile* tiles, int n_tiles,
-                            int direct_block, const void* feat, const void* weights_src, int64_t plane, float* out,
-                            hipStream_t s);
+// MLP inference: out[i] = INR output of the features [level][plane][F] of
+// sample i < n, de-normalized with the block range.  wsrc: first weight of block 0.
+hipError_t launch_mlp_infer(Prec p, const LevelDesc& ld, const MlpDesc& md, const BlockMeta* meta,
+                            const BlockRange* range, int block, const void* wsrc, int n, const void* feat,
+                            int64_t plane, float* out, hipStream_t s);
 
 // Sum slots into gradients and per-block losses; with bump, the last block to
 // finish advances the step counter.
@@ -259,19 +259,34 @@ hipError_t launch_decode_fused(Prec p, const LevelDesc& ld, const MlpDesc& md, c
                                const BlockRange* range, int block, const int32_t* dims, const void* table,
                                const void* wsrc, float* out, hipStream_t s);
 
-// Direct volume rendering by sample streaming (one block's unit cube).
+// INR of block `block` at coords [n][3] in one kernel (arguments as above).
+// Up to here a wave takes as few samples as its lane groups allow (16 levels,
+// 2^17 fp16 entries: 2^15 points 20 us against 30 with four times the samples
+// per wave, 2^16 points 39 against 27).
+constexpr int64_t kQueryFew = 1 << 15;
+hipError_t launch_query(Prec p, const LevelDesc& ld, const MlpDesc& md, const BlockMeta* meta, const BlockRange* range,
+                        int block, const void* table, const void* wsrc, int64_t n, const float* coords, float* out,
+                        hipStream_t s);
+
+// Direct volume rendering of one block's unit cube: samples [k0, k1) of every
+// ray, from the image's current (C, A) when k0 > 0.
 struct RayCamera {
   float eye[3], center[3], up[3];
   float tan_h;                 // tan(vertical field of view / 2)
 };
-hipError_t launch_ray_init(const RayCamera& cam, int width, int height, float* dirs, float* t01, float* rgba,
-                           int32_t* active, int32_t* counter, hipStream_t s);
-hipError_t launch_ray_gen(const RayCamera& cam, const int32_t* active, int n_rays, int k_base, int S, float dt,
-                          const float* dirs, const float* t01, float* coords, hipStream_t s);
-hipError_t launch_ray_shade(const int32_t* active, int n_rays, int k_base, int S, float dt, float opacity_exp,
-                            float alpha_stop, const float* t01, const float* values, const float* tf, int n_tf,
-                            float tf_lo, float tf_inv_range, float* rgba, int32_t* next, int32_t* next_count,
-                            hipStream_t s);
+struct RenderStep {
+  float dt;                    // sample distance
+  float opacity_exp;           // dt / reference step
+  float alpha_stop;
+  float tf_lo, tf_inv_range;
+  int32_t n_tf;
+  int32_t S;                   // samples per round
+};
+constexpr int kRenderSlots = 32;  // counters of the rays' rounds, 64 bytes apart
+hipError_t launch_render(Prec p, const LevelDesc& ld, const MlpDesc& md, const BlockMeta* meta,
+                         const BlockRange* range, int block, const void* table, const void* wsrc,
+                         const RayCamera& cam, int width, int height, const RenderStep& rs, int k0, int k1,
+                         const float* tf, float* image, unsigned long long* rounds, hipStream_t s);
 
 hipError_t launch_voxel_coords(const BlockMeta* meta, int block, int64_t first, int64_t n, float* coords,
                                hipStream_t s);

@@ -97,51 +97,119 @@ struct InferMlp {
     return __builtin_amdgcn_fmed3f(x, 0.0f, inf);
   }
 
-  // Network output of sample c (in every lane group) from the lanes' features.
-  // A: the operands (LDS), in slot order; wo: the output layer's weights of
-  // the neurons that the lane holds (16 m + 4 g + i).
-  __device__ static __forceinline__ float eval(const op_t* __restrict__ A, const f32x4i (&wo)[MT], int lane,
-                                               const op_t (&xb)[KS_IN]) {
-    f32x4i h[MT];
+  // Network outputs of sample c of Q groups of 16 samples (in every lane group)
+  // from the lanes' features.  A: the operands (LDS), in slot order, each read
+  // once for the Q groups, whose chains hide one another's latency; wo: the
+  // output layer's weights of the neurons that the lane holds (16 m + 4 g + i).
+  template <int Q>
+  __device__ static __forceinline__ void eval(const op_t* __restrict__ A, const f32x4i (&wo)[MT], int lane,
+                                              const op_t (&xb)[Q][KS_IN], float (&out)[Q]) {
+    f32x4i h[Q][MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
-      f32x4i acc = {0, 0, 0, 0};
+      f32x4i acc[Q];
 #pragma unroll
-      for (int s = 0; s < KS_IN; ++s) acc = mma(A[(m * KS_IN + s) * 64 + lane], xb[s], acc);
+      for (int q = 0; q < Q; ++q) acc[q] = f32x4i{0, 0, 0, 0};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) h[m][i] = relu(acc[i]);
+      for (int s = 0; s < KS_IN; ++s) {
+        const op_t a = A[(m * KS_IN + s) * 64 + lane];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) acc[q] = mma(a, xb[q][s], acc[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[q][m][i] = relu(acc[q][i]);
     }
 #pragma unroll
     for (int k = 1; k < NH; ++k) {
-      op_t hb[KS_H];
-      if constexpr (BF16) {
+      op_t hb[Q][KS_H];
 #pragma unroll
-        for (int s = 0; s < KS_H; ++s)
+      for (int q = 0; q < Q; ++q)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const int m = 2 * s + j / 4;
-            hb[s][j] = (__bf16)(m < MT ? h[m < MT ? m : 0][j % 4] : 0.0f);
+        for (int s = 0; s < KS_H; ++s) {
+          if constexpr (BF16) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const int m = 2 * s + j / 4;
+              hb[q][s][j] = (__bf16)(m < MT ? h[q][m < MT ? m : 0][j % 4] : 0.0f);
+            }
+          } else {
+            hb[q][s] = h[q][s / 4][s % 4];
           }
-      } else {
-#pragma unroll
-        for (int s = 0; s < KS_H; ++s) hb[s] = h[s / 4][s % 4];
-      }
+        }
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        f32x4i acc = {0, 0, 0, 0};
+        f32x4i acc[Q];
 #pragma unroll
-        for (int s = 0; s < KS_H; ++s) acc = mma(A[(N_IN + ((k - 1) * MT + m) * KS_H + s) * 64 + lane], hb[s], acc);
+        for (int q = 0; q < Q; ++q) acc[q] = f32x4i{0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h[m][i] = relu(acc[i]);
+        for (int s = 0; s < KS_H; ++s) {
+          const op_t a = A[(N_IN + ((k - 1) * MT + m) * KS_H + s) * 64 + lane];
+#pragma unroll
+          for (int q = 0; q < Q; ++q) acc[q] = mma(a, hb[q][s], acc[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) h[q][m][i] = relu(acc[q][i]);
       }
     }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      float o = 0.0f;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o += wo[m][i] * h[q][m][i];
+      o += __shfl_xor(o, 16, 64);
+      o += __shfl_xor(o, 32, 64);
+      out[q] = o;
+    }
+  }
+
+  // Outputs of NQ groups of 16 samples, in fp32 two at a time (in bf16, where
+  // the operands are a sixth of the LDS reads, two spill at four waves per
+  // SIMD): lane group g receives group g's (0 for g >= NQ).  SETS = 4 / NG sets of lane groups hold the
+  // features xb of the groups q = set, set + SETS, ...; the other sets'
+  // features enter a group's product as zeros.
+  template <int NQ, int T>
+  __device__ static __forceinline__ float eval_groups(const op_t* __restrict__ A, const float* __restrict__ wout,
+                                                      int lane, const op_t (&xb)[T][KS_IN]) {
+    constexpr int SETS = 4 / NG, Q = !BF16 && NQ >= 2 ? 2 : 1;
+    static_assert(NQ == SETS * T && NQ % Q == 0, "every group's features are in one set");
+    const int g = lane / 16, set = g / NG;
+    f32x4i wo[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) wo[m] = *reinterpret_cast<const f32x4i*>(&wout[16 * m + 4 * g]);
     float o = 0.0f;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int q0 = 0; q0 < NQ; q0 += Q) {
+      __builtin_amdgcn_sched_barrier(0);  // (more groups in flight would not fit the registers)
+      op_t xq[Q][KS_IN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o += wo[m][i] * h[m][i];
-    o += __shfl_xor(o, 16, 64);
-    o += __shfl_xor(o, 32, 64);
+      for (int u = 0; u < Q; ++u)
+#pragma unroll
+        for (int s = 0; s < KS_IN; ++s) {
+          const int q = q0 + u;
+          xq[u][s] = xb[q / SETS][s];
+          if constexpr (SETS > 1) {
+            if (set != q % SETS) {
+              if constexpr (BF16) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) xq[u][s][j] = (__bf16)0.0f;
+              } else {
+                xq[u][s] = 0.0f;
+              }
+            }
+          }
+        }
+      float v[Q];
+      eval<Q>(A, wo, lane, xq, v);
+#pragma unroll
+      for (int u = 0; u < Q; ++u)
+        if (g == q0 + u) o = v[u];
+    }
     return o;
   }
 };

@@ -458,108 +458,12 @@ __global__ __launch_bounds__(64 * NW, MINW) void k_mlp_train(MlpDesc md, int F, 
   flush(cur_block);
 }
 
-// ---------------------------------------------------------------------------
-// Inference kernel: forward only, output de-normalized with the block range.
-// Direct tiles (tiles == nullptr): samples [0, n) of block `block0`.
-// ---------------------------------------------------------------------------
-template <class TR, int W, int NH, typename FT, typename WSRC>
-__global__ __launch_bounds__(256) void k_mlp_infer(MlpDesc md, int F, const BlockMeta* __restrict__ meta,
-                                                   const BlockRange* __restrict__ range,
-                                                   const BlockPlan* __restrict__ plan,
-                                                   const Tile* __restrict__ tiles, int n_tiles, int direct_block,
-                                                   const FT* __restrict__ feat, const WSRC* __restrict__ wsrc_all,
-                                                   int64_t plane, float* __restrict__ out, int64_t n_table_params) {
-  using S = MlpShape<TR, W, NH>;
-  using op_t = typename TR::op_t;
-  extern __shared__ __align__(16) unsigned char smem[];
-  op_t* A = reinterpret_cast<op_t*>(smem);
-  float* wout = reinterpret_cast<float*>(smem + sizeof(op_t) * S::N_SLOTS * 64);
-  Tile tl;
-  int64_t base;
-  if (tiles) {
-    tl = tiles[blockIdx.x];
-    base = plan[tl.block].sample_off + tl.start;
-  } else {  // direct: samples [0, n_tiles) of block direct_block
-    tl.block = direct_block;
-    base = (int64_t)blockIdx.x * kTile;
-    tl.count = (int)min((int64_t)kTile, (int64_t)n_tiles - base);
-  }
-  const WSRC* ws = wsrc_all + meta[tl.block].param_off + n_table_params;
-  load_weights<TR, W, NH>(ws, md, A, wout);
-  __syncthreads();
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int g = lane / 16, c = lane % 16;
-  const BlockRange br = range[tl.block];
-  int fo[S::KS_IN * TR::VPL];  // element offsets of this lane's features (-1 past the input width)
-#pragma unroll
-  for (int s = 0; s < S::KS_IN; ++s)
-#pragma unroll
-    for (int j = 0; j < TR::VPL; ++j) {
-      const int f = 8 * g + s * TR::VPL + j;
-      fo[s * TR::VPL + j] = f < md.in_dim ? (f / F) * (int)plane * F + f % F : -1;
-    }
-  for (int q = 0; q < 4; ++q) {
-    const int sl = wave * 64 + q * 16 + c;
-    const bool valid = sl < tl.count;
-    const int64_t gi = base + sl;
-    op_t xb[S::KS_IN];
-#pragma unroll
-    for (int s = 0; s < S::KS_IN; ++s)
-#pragma unroll
-      for (int j = 0; j < TR::VPL; ++j) {
-        const int o = fo[s * TR::VPL + j];
-        const float v = (float)feat[(valid && o >= 0) ? o + (int)gi * F : 0];  // unconditional load
-        TR::put(xb[s], j, (valid && o >= 0) ? v : 0.0f);
-      }
-    f32x4 h[S::MT];
-#pragma unroll
-    for (int m = 0; m < S::MT; ++m) {
-      f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < S::KS_IN; ++s) acc = TR::mma(A[(m * S::KS_IN + s) * 64 + lane], xb[s], acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h[m][i] = fmaxf(acc[i], 0.0f);
-    }
-#pragma unroll
-    for (int k = 1; k < NH; ++k) {
-      op_t hb[S::KS_H];
-      pack_b<TR, S::MT, S::KS_H>(h, hb);
-      f32x4 hn[S::MT];
-#pragma unroll
-      for (int m = 0; m < S::MT; ++m) {
-        f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < S::KS_H; ++s)
-          acc = TR::mma(A[(S::N_A0 + ((k - 1) * S::MT + m) * S::KS_H + s) * 64 + lane], hb[s], acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) hn[m][i] = fmaxf(acc[i], 0.0f);
-      }
-#pragma unroll
-      for (int m = 0; m < S::MT; ++m) h[m] = hn[m];
-    }
-    float op = 0.0f;
-#pragma unroll
-    for (int m = 0; m < S::MT; ++m)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) op += wout[16 * m + 4 * g + i] * h[m][i];
-    op += __shfl_xor(op, 16, 64);
-    op += __shfl_xor(op, 32, 64);
-    if (valid && g == 0) out[gi] = op * br.range + br.vmin;
-  }
-}
-
 template <class TR, int W, int NH, int NW>
 static size_t train_smem() {
   using S = MlpShape<TR, W, NH>;
   return sizeof(typename TR::op_t) * S::N_SLOTS * 64 + sizeof(float) * (64 + NW * 65 + 4) +
          sizeof(typename TR::st_t) * S::ROWS * (NW == 4 ? S::RS : S::DWS) * NW;
 }
-template <class TR, int W, int NH>
-static size_t infer_smem() {
-  using S = MlpShape<TR, W, NH>;
-  return sizeof(typename TR::op_t) * S::N_SLOTS * 64 + sizeof(float) * 64;
-}
-
 template <class TR, int W, int NH, typename FT, typename WSRC, int MINW = 1, int NW = 4>
 static hipError_t run_train(const MlpDesc& md, int F, const BlockMeta* meta, const BlockPlan* plan, const Tile* tiles,
                             int n_tiles, const void* feat, const float* target, const void* wsrc, float* dfeat,
@@ -571,21 +475,6 @@ static hipError_t run_train(const MlpDesc& md, int F, const BlockMeta* meta, con
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NW), sm, s, md, F, meta, plan, tiles, n_tiles, (const FT*)feat,
                      target, (const WSRC*)wsrc, dfeat, plane, slots, slot_stride, n_table, l1);
-  return hipGetLastError();
-}
-
-template <class TR, int W, int NH, typename FT, typename WSRC>
-static hipError_t run_infer(const MlpDesc& md, int F, const BlockMeta* meta, const BlockRange* range,
-                            const BlockPlan* plan, const Tile* tiles, int n_tiles, int direct_block, const void* feat,
-                            const void* wsrc, int64_t plane, float* out, int64_t n_table, hipStream_t s) {
-  const size_t sm = infer_smem<TR, W, NH>();
-  auto kern = k_mlp_infer<TR, W, NH, FT, WSRC>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-  if (e != hipSuccess) return e;
-  const int grid = tiles ? n_tiles : (n_tiles + kTile - 1) / kTile;
-  if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), sm, s, md, F, meta, range, plan, tiles, n_tiles, direct_block,
-                     (const FT*)feat, (const WSRC*)wsrc, plane, out, n_table);
   return hipGetLastError();
 }
 
@@ -616,24 +505,6 @@ hipError_t launch_mlp_train(Prec p, const MlpDesc& md, const LevelDesc& ld, cons
                                                         (int64_t)0, loss_l1, s);                                           \
     return run_train<TrF32, WW, NN, float, float>(md, ld.F, meta, plan, tiles, n_tiles, feat, target, weights_src, \
                                                    dfeat, plane, slots, slot_stride, grid, (int64_t)0, loss_l1, s); \
-  }
-  DVNR_MLP_SHAPES(X)
-#undef X
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_mlp_infer(Prec p, const MlpDesc& md, const LevelDesc& ld, const BlockMeta* meta,
-                            const BlockRange* range, const BlockPlan* plan, const Tile* tiles, int n_tiles,
-                            int direct_block, const void* feat, const void* weights_src, int64_t plane, float* out,
-                            hipStream_t s) {
-  if ((int64_t)md.in_dim * plane >= ((int64_t)1 << 31)) return hipErrorInvalidValue;  // 32-bit feature offsets
-#define X(WW, NN)                                                                                                 \
-  if (md.width == WW && md.n_hidden == NN) {                                                                      \
-    if (p == Prec::MIXED)                                                                                         \
-      return run_infer<TrBF16, WW, NN, __bf16, __bf16>(md, ld.F, meta, range, plan, tiles, n_tiles, direct_block, \
-                                                        feat, weights_src, plane, out, (int64_t)0, s);            \
-    return run_infer<TrF32, WW, NN, float, float>(md, ld.F, meta, range, plan, tiles, n_tiles, direct_block, feat, \
-                                                   weights_src, plane, out, (int64_t)0, s);                       \
   }
   DVNR_MLP_SHAPES(X)
 #undef X

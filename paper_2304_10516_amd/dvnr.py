@@ -273,8 +273,7 @@ class DVNR:
         camera (unit-cube coordinates of the block); tf: [n][4] RGBA over
         tf_range (float32, on the device).  Returns the premultiplied RGBA image
         [height][width][4] (written into `out` when given).  static_scratch:
-        call dvnr_render_static, which keeps the ray state in the library's
-        static device array instead of a workspace allocated here."""
+        call dvnr_render_static, which takes no workspace."""
         cam = L.Camera((C.c_float * 3)(*eye), (C.c_float * 3)(*center), (C.c_float * 3)(*up), float(fovy_deg),
                        int(width), int(height))
         tf = tf.to(device=self.device, dtype=torch.float32).contiguous()

@@ -90,3 +90,34 @@ def test_render_early_termination():
     assert np.all(img[..., 3][stopped] >= 0.8)
     assert np.mean(err.max(axis=-1) <= 5e-5) >= 0.99
     assert err.max() <= 0.2 + 5e-5  # the opacity left at the limit bounds a shifted stopping sample
+
+
+def test_render_long_rays_over_several_launches():
+    """A step so small that a ray's samples take two launches (4096 samples
+    each): image and sample count as if they were one march.  Each of the n
+    compositing steps rounds (C, A) once more than the oracle's."""
+    say("render fp32, thousands of samples per ray")
+    model, lay, pe, vmin, vmax = _model("fp32")
+    cam = o.Camera(eye=(1.9, 1.4, 2.3), center=(0.5, 0.5, 0.5), up=(0.0, 1.0, 0.0), fovy_deg=40.0, width=9, height=7)
+    lo, hi = vmin - 0.1 * (vmax - vmin), vmax
+    dt, ref = 1.0 / 6000, 1.0 / 8
+    for stop in (1.0, 0.7):
+        img = model.render(0, cam.eye, cam.center, cam.up, cam.fovy_deg, cam.width, cam.height,
+                           torch.tensor(TF, dtype=torch.float32), (lo, hi), dt, ref, alpha_stop=stop,
+                           samples_per_round=50).cpu().numpy()
+        ref_img = o.render(lay, pe, vmin, vmax, cam, TF, lo, hi, dt, ref, alpha_stop=stop)
+        org, d = o.camera_rays(cam)
+        t0, t1 = o.ray_box(org, d)
+        n = max(int((t1 - t0).max() / dt), 1)
+        assert n > 4096
+        err = np.abs(img - ref_img).max()
+        # the sample that reaches the limit may shift by a few, each of opacity 1 - (1 - 0.9)^(dt / ref) at most
+        slack = 5e-5 + n * 2.0 ** -24 + (0.0 if stop == 1.0 else 4 * (1 - 0.1 ** (dt / ref)))
+        say(f"alpha_stop {stop}: max abs diff {err:.2e} (bar {slack:.2e}), {model.last_render_samples} samples")
+        assert err <= slack
+        if stop == 1.0 and ref_img[..., 3].max() < 1.0:
+            rounds = 0
+            for a, b in zip(t0[t1 > t0], t1[t1 > t0]):
+                k = np.arange(int((b - a) / dt) + 3)
+                rounds += int((~o.sample_params(a, b, dt, k)[1]).argmax()) // 50 + 1
+            assert model.last_render_samples == rounds * 50
