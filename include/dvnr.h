@@ -364,7 +364,8 @@ dvnr_status dvnr_debug_indices(dvnr_t* h, int32_t level, int64_t n, const float*
  * with the "profile_phases" option since the previous call (those steps run
  * eagerly, with HIP events on the training stream between the phases):
  * ms[0] sampler, [1] encoding forward, [2] MLP forward/loss/backward,
- * [3] encoding backward of the bin-privatized levels, [4] encoding backward
+ * [3] encoding backward of the levels summed in LDS (bin-privatized, or by
+ * whole tables), [4] encoding backward
  * by direct atomics, [5] and [6] the two passes of the destination-partitioned
  * encoding backward (bucketing, slice sums), [7] weight-gradient reduction,
  * [8] Adam; `ms` holds DVNR_N_PHASES doubles.  *n_steps (may be NULL)
@@ -387,8 +388,9 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
 
 /* Layout of the current training plan (the last samples_per_step given to
  * dvnr_train_steps): spatial bins per axis of the ordered sampler and the
- * number of coarse levels whose encoding backward is bin-privatized (levels
- * [0, *priv_levels)); 0 when ordered sampling is off.  Any pointer may be NULL. */
+ * number of coarse levels whose encoding backward is summed in LDS, per bin or
+ * by whole tables (levels [0, *priv_levels)); 0 when ordered sampling is off.
+ * Any pointer may be NULL. */
 dvnr_status dvnr_plan_info(const dvnr_t* h, int32_t* bins_per_axis, int32_t* priv_levels);
 
 /* First level of the current training plan whose encoding backward is
@@ -434,7 +436,9 @@ dvnr_status dvnr_set_loss(dvnr_t* h, int32_t loss, double boundary_frac, double 
  *  "spatial_sort"    0/1 : store each step's samples grouped by spatial bin
  *                          (default 1 for mixed, 0 for fp32); enables the
  *                          bin-privatized backward of the coarse levels
- *  "priv_levels"     n   : privatize levels [0, n) (-1: chosen per plan)
+ *  "priv_levels"     n   : privatize levels [0, n) (-1: chosen per plan; tables
+ *                          of at most 16384 floats are then summed whole in LDS,
+ *                          unless "priv_classes" or "scatter_concurrent" is set)
  *  "sample_ahead"  0..3 : with ordered sampling and graph replays, draw step
  *                          i + 1's samples on a third stream while step i
  *                          trains (two sample sets), forked at the start of

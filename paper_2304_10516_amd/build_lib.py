@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libdvnr.so")
 WIDTHS = (16, 32, 64)  # networks' widths, a translation unit each
 SOURCES = [f"k_{part}_w{w}.hip" for w in WIDTHS for part in ("render", "query", "decode")] + [
     "dvnr_host.hip", "k_core.hip", "k_mlp.hip", "k_mlp_blocks.hip", "k_sort.hip", "k_infer.hip", "k_encode_bin.hip",
-    "k_scatter_part.hip", "micro.hip"]
+    "k_scatter_part.hip", "k_scatter_table.hip", "micro.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

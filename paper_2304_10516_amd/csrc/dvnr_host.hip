@@ -89,6 +89,7 @@ struct dvnr {
   int priv_levels = -1;  // -1: chosen per plan
   int sort_bins = 0;     // bins per axis of ordered sampling (0: at least kBinSamples samples per bin)
   int sort_B = 0, priv_L = 0, n_groups = 0;
+  int table_chunks = 0;  // workgroups per block and level of the whole-table backward (0: not used)
   int priv_small = 0, priv_direct = 0;  // LDS classes: small [0, priv_small), large up to priv_direct, then direct
   int priv_classes = -1;  // launch the privatized levels by LDS class (0: one launch; -1: one block, partitioned)
   int encode_binned = 0;                // ordered samples: LDS-staged encoding of the levels whose box fits
@@ -650,6 +651,22 @@ static dvnr_status plan_partition(dvnr_t* h, const std::vector<int64_t>& n, hipS
   return DVNR_OK;
 }
 
+// Workgroups per block and level of the whole-table backward
+// (launch_scatter_table), or 0 where the privatized kernel takes the levels
+// below the partitioned ones: the whole-table form replaces it where each of
+// these levels' tables fits LDS and no option asks for a privatized form.
+// More workgroups sum in LDS at once, fewer add less to memory: the two are
+// equal at about sqrt(n) / 4 workgroups (65,536 samples, 4 levels of 2^11 x 4:
+// n^(1/2) / 8 33 us, / 4 22 us; / 2 within the noise of / 4 in the step).
+static int table_chunks(const dvnr_t* h, const std::vector<int64_t>& n) {
+  if (h->priv_levels >= 0 || h->priv_classes >= 0 || h->scatter_concurrent) return 0;
+  for (int l = 0; l < h->part_l0; ++l)
+    if (!scatter_table_fits(h->ld, l)) return 0;
+  const double most = (double)*std::max_element(n.begin(), n.end());
+  const int room = std::max(1, 2048 / (h->nb * std::max(h->part_l0, 1)));  // one launch: a few rounds of the chip
+  return std::max(1, std::min({(int)std::lround(std::sqrt(most) / 4.0), 128, room}));
+}
+
 static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_t s) {
   int64_t total = 0;
   for (auto v : n) total += v;
@@ -754,6 +771,7 @@ static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_
     dvnr_status st = plan_partition(h, n, s);
     if (st) return st;
   }
+  h->table_chunks = table_chunks(h, n);
   HIPCHK(hipMemcpyAsync(h->d_plan(), h->hplan.data(), sizeof(BlockPlan) * h->nb, hipMemcpyHostToDevice, s));
   if (h->n_tiles)
     HIPCHK(hipMemcpyAsync(h->d_tiles(), h->htiles.data(), sizeof(Tile) * h->n_tiles, hipMemcpyHostToDevice, s));
@@ -946,6 +964,11 @@ static dvnr_status enqueue_step(dvnr_t* h, int gen, hipStream_t s, int set = 0, 
     HIPCHK(part_accum(h->side));
     HIPCHK(hipEventRecord(h->ev_join2, h->side));
   }
+  // levels whose whole tables fit LDS: one launch for all of them
+  const bool whole = sorted && h->table_chunks > 0;
+  if (whole)
+    HIPCHK(launch_scatter_table(h->ld, 0, lp, h->table_chunks, h->nb, h->d_meta(), h->d_plan(), h->d_coords(set),
+                                h->d_dfeat(), h->max_batch * F, (float*)h->buf.grads, s));
   // privatized levels [0, lp) in up to three launches by LDS class: small boxes
   // (coarse levels, high occupancy), large boxes, and levels whose boxes never
   // fit (direct atomics over each bin's samples, no LDS).  Plain workgroup
@@ -974,7 +997,7 @@ static dvnr_status enqueue_step(dvnr_t* h, int gen, hipStream_t s, int set = 0, 
     }
     const int cls[3][3] = {{0, a, 1}, {a, c, 2}, {c, conc ? c : lp, 0}};
     for (const auto& r : cls)
-      if (r[1] > r[0])
+      if (r[1] > r[0] && !whole)
         HIPCHK(launch_scatter_priv(h->ld, r[0], r[1], h->sort_B, h->nb, h->d_meta(), h->d_plan(), h->d_binstart(set),
                                    h->d_coords(set), h->d_dfeat(), h->max_batch * F, (float*)h->buf.grads, 0, r[2],
                                    s));
@@ -1703,12 +1726,7 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
     const int save_update = h->apply_update, save_profile = h->profile;
     const int64_t saved_step = h->host_step;
     const std::vector<int64_t> n = apportion(h, samples_per_step);
-    // the automatic privatized-level count of this plan
-    h->priv_levels = -1;
-    h->spatial_sort = 1;
-    st = set_plan(h, n, s);
-    if (st) return st;
-    const int auto_pl = h->priv_L, L = h->enc.n_levels;
+    const int auto_pl = -1, L = h->enc.n_levels;  // (as planned without the option)
     struct Cand {
       int sort, priv, cap;
     };
@@ -1834,10 +1852,12 @@ dvnr_status dvnr_set_option(dvnr_t* h, const char* name, int64_t value) {
     h->part_concurrent = value ? 1 : 0;
   } else if (n == "scatter_concurrent") {
     h->scatter_concurrent = value ? 1 : 0;
+    h->plan_total = -1;  // the choice of the whole-table backward depends on it
   } else if (n == "encode_binned") {
     h->encode_binned = value ? 1 : 0;
   } else if (n == "priv_classes") {
     h->priv_classes = value < 0 ? -1 : (value ? 1 : 0);
+    h->plan_total = -1;  // the choice of the whole-table backward depends on it
   } else if (n == "scatter_strided") {
     h->scatter_strided = value ? 1 : 0;
   } else if (n == "xcd_map") {

@@ -209,6 +209,15 @@ hipError_t launch_scatter_priv(const LevelDesc& ld, int l0, int l1, int B, int n
                                const float* dfeat, int64_t ls, float* grad, int xcd_map, int size_class,
                                hipStream_t s);
 
+// Encoding backward of levels [l0, l1) whose whole gradient tables fit LDS
+// (scatter_table_fits): `chunks` workgroups per block and level, each summing
+// its share of the block's samples into a copy of the table.
+constexpr int kTableAcc = 16384;  // 64-bit accumulators of one table copy (128 KB of LDS)
+bool scatter_table_fits(const LevelDesc& ld, int l);
+hipError_t launch_scatter_table(const LevelDesc& ld, int l0, int l1, int chunks, int n_blocks, const BlockMeta* meta,
+                                const BlockPlan* plan, const float* coords, const float* dfeat, int64_t ls,
+                                float* grad, hipStream_t s);
+
 // MLP training pass (forward, L2 loss, backward) on MFMA; writes dfeat
 // (level-major f32) and per-wave dW/loss partials into slots.  min_waves:
 // waves per SIMD the 4-wave kernel's registers allow (1 or 2); wg_waves: 8
