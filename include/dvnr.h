@@ -442,9 +442,10 @@ dvnr_status dvnr_set_loss(dvnr_t* h, int32_t loss, double boundary_frac, double 
  *  "sample_ahead"  0..3 : with ordered sampling and graph replays, draw step
  *                          i + 1's samples on a third stream while step i
  *                          trains (two sample sets), forked at the start of
- *                          step i (1), after its encoding (2, the default)
- *                          or after its MLP (3); 0: off.  The first step of
- *                          each training call draws its own.
+ *                          step i (1), after its encoding (2) or after its
+ *                          MLP (3); 0: off.  The first step of each training
+ *                          call draws its own.  Until set: 2, or 0 for plans
+ *                          of few samples whose tables are summed whole in LDS.
  *  "sort_bins"       n   : spatial bins per axis of ordered sampling, 1..8
  *                          (0, the default: the most that keep at least 192
  *                          samples per bin in the block with the fewest)

@@ -60,6 +60,8 @@ struct dvnr {
 
   // current training plan
   int64_t plan_total = -1;
+  std::vector<int64_t> plan_n;  // samples per block of the plan in the workspace
+  bool plan_valid = false;      // it still stands (no option, loss or binding changed since)
   int n_tiles = 0, mlp_grid = 0;
   std::vector<BlockPlan> hplan;
   std::vector<Tile> htiles;
@@ -107,7 +109,6 @@ struct dvnr {
   double prof_ms[kPhases] = {};
   hipGraphExec_t graph = nullptr;
   hipStream_t graph_stream = nullptr;
-  int64_t graph_total = -1;
 
   unsigned char* ws() const { return (unsigned char*)buf.workspace; }
   BlockMeta* d_meta() const { return (BlockMeta*)(ws() + o_meta); }
@@ -147,7 +148,7 @@ struct dvnr {
              ev_join3 = nullptr;
   // sampler look-ahead (option "sample_ahead", graph replays with ordered
   // sampling): a third stream draws step i + 1's samples while step i trains
-  int sample_ahead = 2;
+  int sample_ahead = -1;  // -1: chosen per plan (ahead_point)
   hipStream_t ahead = nullptr;
   hipEvent_t ev_fork4 = nullptr, ev_join4 = nullptr;
   hipGraphExec_t graph_ahead[2] = {nullptr, nullptr};  // the step on sample set p, drawing into 1 - p
@@ -177,6 +178,20 @@ struct dvnr {
     if (ahead) (void)hipStreamDestroy(ahead);
   }
 };
+
+// Point of a replayed step at which the next step's sampler forks off (0: the
+// step draws its own samples).  A fork and a join between queues cost about 8 us
+// each; where the step is a short chain of kernels on one stream (the
+// whole-table backward, few samples) that is more than the sampler's own time:
+// 4,096 samples 51 us a step with the look-ahead, 43 without; 65,536 samples
+// 103 / 82; 217,000 samples of 16 levels 157 / 165.
+static int ahead_point(const dvnr* h) {
+  constexpr int64_t kFew = 1 << 17;
+  if (h->sample_ahead >= 0) return h->sample_ahead;
+  int64_t total = 0;
+  for (auto v : h->plan_n) total += v;
+  return h->table_chunks > 0 && total <= kFew ? 0 : 2;
+}
 
 // Drop the captured step graphs (their kernels' arguments no longer hold).
 static void drop_graphs(dvnr_t* h) {
@@ -461,6 +476,7 @@ dvnr_status dvnr_bind(dvnr_t* h, const dvnr_buffers* b) {
     HIPCHK(hipMemset(h->d_ring(), 0, sizeof(float) * kLossRing * h->nb));
     h->host_step = 0;
     h->plan_total = -1;
+    h->plan_valid = false;
     drop_graphs(h);
     h->bound = true;
     h->prepared = false;
@@ -667,7 +683,18 @@ static int table_chunks(const dvnr_t* h, const std::vector<int64_t>& n) {
   return std::max(1, std::min({(int)std::lround(std::sqrt(most) / 4.0), 128, room}));
 }
 
+// The plan (and the step graphs captured on it) stays where the same counts are
+// asked for again, as by one bounded training run after another (16 steps of
+// 65,536 samples: building, uploading and capturing again took 0.2 of 1.6 ms).
 static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_t s) {
+  if (h->plan_valid && n == h->plan_n) {
+    // a plan cannot be built under capture: nor is one used there that happens to stand
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHK(hipStreamIsCapturing(s, &cs));
+    if (cs != hipStreamCaptureStatusNone) return fail(DVNR_E_STATE, "a plan is not made while its stream is captured");
+    return DVNR_OK;
+  }
+  h->plan_valid = false;
   int64_t total = 0;
   for (auto v : n) total += v;
   if (total > h->max_batch) return fail(DVNR_E_INVALID, "samples per step exceed max_batch");
@@ -772,6 +799,7 @@ static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_
     if (st) return st;
   }
   h->table_chunks = table_chunks(h, n);
+  h->plan_n = n;
   HIPCHK(hipMemcpyAsync(h->d_plan(), h->hplan.data(), sizeof(BlockPlan) * h->nb, hipMemcpyHostToDevice, s));
   if (h->n_tiles)
     HIPCHK(hipMemcpyAsync(h->d_tiles(), h->htiles.data(), sizeof(Tile) * h->n_tiles, hipMemcpyHostToDevice, s));
@@ -781,6 +809,7 @@ static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_
   HIPCHK(hipMemcpyAsync(h->d_grange(), h->hgrange.data(), sizeof(int32_t) * 2 * h->nb, hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
   drop_graphs(h);
+  h->plan_valid = true;
   return DVNR_OK;
 }
 
@@ -858,7 +887,7 @@ static dvnr_status enqueue_step(dvnr_t* h, int gen, hipStream_t s, int set = 0, 
   // step that option sample_ahead names (1: its start, 2: after the encoding,
   // 3: after the MLP)
   auto fork_ahead = [&](int at) -> dvnr_status {
-    if (!ahead || h->sample_ahead != at) return DVNR_OK;
+    if (!ahead || ahead_point(h) != at) return DVNR_OK;
     if (!h->ahead) {
       HIPCHK(hipStreamCreateWithFlags(&h->ahead, hipStreamNonBlocking));
       HIPCHK(hipEventCreateWithFlags(&h->ev_fork4, hipEventDisableTiming));
@@ -1074,7 +1103,7 @@ static dvnr_status train_ready(dvnr_t* h) {
 }
 
 // n_steps generated-sample steps with the current plan: replays of one
-// captured step (hipGraph, keyed by stream and `plan_key`) on a non-default
+// captured step (hipGraph of the current plan, keyed by stream) on a non-default
 // stream, else eager launches.  Losses of the steps go to loss_out (device
 // float [n_steps][n_blocks]) when given.
 // Capture one step as a graph (kernel arguments are fixed at capture).
@@ -1091,7 +1120,7 @@ static dvnr_status capture_step(dvnr_t* h, hipStream_t s, int set, bool ahead, h
   return DVNR_OK;
 }
 
-static dvnr_status run_steps(dvnr_t* h, int64_t n_steps, int64_t plan_key, float* loss_out, hipStream_t s) {
+static dvnr_status run_steps(dvnr_t* h, int64_t n_steps, float* loss_out, hipStream_t s) {
   dvnr_status st = DVNR_OK;
   const int64_t s0 = h->host_step;
   int64_t done = 0;
@@ -1100,16 +1129,15 @@ static dvnr_status run_steps(dvnr_t* h, int64_t n_steps, int64_t plan_key, float
   // every replayed step trains on set p and draws the next step's into 1 - p
   // (the last step's draw is not used).  No drawn samples outlive the call,
   // so changes of the volumes or ranges between calls are always seen.
-  const bool ahead = graph_ok && h->sample_ahead && h->spatial_sort && h->n_groups > 0 && n_steps > 0;
+  const bool ahead = graph_ok && ahead_point(h) && h->spatial_sort && h->n_groups > 0 && n_steps > 0;
   if (ahead) {
-    if (!h->graph_ahead[0] || h->graph_stream != s || h->graph_total != plan_key) {
+    if (!h->graph_ahead[0] || h->graph_stream != s) {
       drop_graphs(h);
       for (int p = 0; p < 2; ++p) {
         st = capture_step(h, s, p, true, &h->graph_ahead[p]);
         if (st) return st;
       }
       h->graph_stream = s;
-      h->graph_total = plan_key;
     }
     st = enqueue_sorted_sample(h, 0, 0, s);
     if (st) return st;
@@ -1119,12 +1147,11 @@ static dvnr_status run_steps(dvnr_t* h, int64_t n_steps, int64_t plan_key, float
     const int64_t chunk = std::min<int64_t>(n_steps - done, kLossRing);
     if (ahead) {
       for (int64_t k = 0; k < chunk; ++k, set ^= 1) HIPCHK(hipGraphLaunch(h->graph_ahead[set], s));
-    } else if (graph_ok && (!h->graph || h->graph_stream != s || h->graph_total != plan_key)) {
+    } else if (graph_ok && (!h->graph || h->graph_stream != s)) {
       drop_graphs(h);
       st = capture_step(h, s, 0, false, &h->graph);
       if (st) return st;
       h->graph_stream = s;
-      h->graph_total = plan_key;
     }
     for (int64_t k = 0; k < chunk && !ahead; ++k) {
       if (graph_ok) {
@@ -1159,7 +1186,7 @@ dvnr_status dvnr_train_steps(dvnr_t* h, int32_t n_steps, int64_t samples_per_ste
       if (st) return st;
       h->plan_total = samples_per_step;
     }
-    return run_steps(h, n_steps, samples_per_step, loss_out, s);
+    return run_steps(h, n_steps, loss_out, s);
   } catch (...) {
     return fail(DVNR_E_INVALID, "train failed");
   }
@@ -1211,7 +1238,7 @@ dvnr_status dvnr_train_until(dvnr_t* h, const dvnr_stop_policy* pol, int64_t sam
       }
       const int64_t next_check = use_loss ? (done / pol->check_every + 1) * pol->check_every : INT64_MAX;
       const int64_t chunk = std::min(next_end, next_check) - done;
-      st = run_steps(h, chunk, -2, nullptr, s);
+      st = run_steps(h, chunk, nullptr, s);
       if (st) return st;
       done += chunk;
       for (int b = 0; b < h->nb; ++b)
@@ -1747,6 +1774,7 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
       h->spatial_sort = c.sort;
       h->priv_levels = c.priv;
       h->mlp_cap = c.cap;
+      h->plan_valid = false;
       st = set_plan(h, n, s);
       if (st) break;
       for (int k = 0; k < 2 && !st; ++k) st = enqueue_step(h, 1, s);
@@ -1778,6 +1806,7 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
     h->spatial_sort = pick.sort;
     h->priv_levels = pick.priv;
     h->mlp_cap = pick.cap;
+    h->plan_valid = false;
     st = set_plan(h, n, s);
     if (st) return st;
     h->plan_total = samples_per_step;
@@ -1883,6 +1912,7 @@ dvnr_status dvnr_set_option(dvnr_t* h, const char* name, int64_t value) {
   } else {
     return fail(DVNR_E_INVALID, "unknown option " + n);
   }
+  h->plan_valid = false;
   drop_graphs(h);
   return DVNR_OK;
 }
@@ -1896,6 +1926,7 @@ dvnr_status dvnr_set_loss(dvnr_t* h, int32_t loss, double boundary_frac, double 
   h->bnd_frac = boundary_frac;
   h->bnd_sigma = sigma;
   h->plan_total = -1;  // per-block boundary counts live in the plan
+  h->plan_valid = false;
   drop_graphs(h);
   return DVNR_OK;
 }
