@@ -265,15 +265,16 @@ static int64_t level_entries(const dvnr_t* h, int l) {
 }
 
 // Sub-bucket capacity: 1.25x the mean load of a block's (slice, sub-bucket)
-// plus 8 records.  Sub-buckets per bucket: about one per 512 records of the
+// plus 8 records (4 records, one per cell edge along x, and a few single
+// corners per sample).  Sub-buckets per bucket: about one per 256 records of the
 // lightest bucket, a power of two in [1, kPartSub]; then a level's ns * nsub
 // <= max(ns, 8 n / 512) for every block, so its records are at most
-// 10 n + 9 (kPartMaxSlices + n / 64) per block (the workspace bound).
+// 5 n + 9 (kPartMaxSlices + n / 64) per block (the workspace bound).
 static int64_t part_bucket_cap(int64_t n, int ns, int nsub) {
-  return n > 0 ? (10 * n + (int64_t)ns * nsub - 1) / ((int64_t)ns * nsub) + 8 : 0;
+  return n > 0 ? (5 * n + (int64_t)ns * nsub - 1) / ((int64_t)ns * nsub) + 8 : 0;
 }
 static int64_t part_level_records(int64_t max_batch, int n_blocks) {
-  return 10 * max_batch + 9 * (max_batch / 64 + 1) + (int64_t)9 * kPartMaxSlices * n_blocks;
+  return 5 * max_batch + 9 * (max_batch / 64 + 1) + (int64_t)9 * kPartMaxSlices * n_blocks;
 }
 
 extern "C" {
@@ -400,7 +401,7 @@ dvnr_status dvnr_create(const dvnr_encoding* enc, const dvnr_mlp* mlp, const dvn
       h->o_ptmax = take(sizeof(float) * nl * h->max_tiles);
       h->o_povf = take(sizeof(uint8_t) * kPartMaxSlices * nl * n_blocks);
       h->o_pcur = take(sizeof(int32_t) * kPartSub * kPartMaxSlices * nl * n_blocks);
-      h->o_precs = take(sizeof(uint32_t) * (1 + e.n_features) * nl * part_level_records(max_batch, n_blocks));
+      h->o_precs = take(sizeof(uint32_t) * (e.n_features == 2 ? 3 : 2 + e.n_features) * nl * part_level_records(max_batch, n_blocks));
     }
     h->spatial_sort = (h->prec == Prec::MIXED) ? 1 : 0;
     h->ws_bytes = o;

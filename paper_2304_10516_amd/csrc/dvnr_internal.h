@@ -155,9 +155,9 @@ struct PartBlock {
   int32_t cap[kMaxLevels];
   int32_t tile0, ntiles;
 };
-// Pass 1 over the tiles: every (sample, corner) contribution of the levels is
-// appended, as one record of 1 + F words (slice << 16 | entry within the
-// slice, then F floats), to its slice's bucket (sub-bucket tile % nsub);
+// Pass 1 over the tiles: the two contributions of every cell edge along x are
+// appended, as one record of 2 + F words (3 for F = 2; two records where the
+// edge crosses slices), to their slice's bucket (sub-bucket tile % nsub);
 // a full sub-bucket's overflow is added to `grad` directly; tmax[(l - l0) *
 // n_tiles + tile] receives the tile's largest |contribution|.  Pass 2: one
 // workgroup per (block, level, slice) sums its bucket in LDS (64-bit fixed

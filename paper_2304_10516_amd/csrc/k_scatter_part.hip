@@ -7,9 +7,10 @@
 // per contribution is paid at the L2 atomic units' request rate.  Here the
 // contributions are instead routed to their destination.  The table of such a
 // level is cut into slices of up to kPartSliceMax fp32 accumulators (LDS):
-//   pass 1 (k_part_bucket), one workgroup per (tile of samples, level): the 8
-//     corner entries and contributions w * dL/dy of each sample become
-//     records, counting-sorted by slice in LDS; one global atomic per
+//   pass 1 (k_part_bucket), one workgroup per (tile of samples, level): the 4
+//     cell edges along x of each sample, both corners' entries and
+//     contributions w * dL/dy, become records (two where an edge crosses
+//     slices), counting-sorted by slice in LDS; one global atomic per
 //     (workgroup, nonempty slice) reserves room in that slice's bucket, and
 //     each slice's run of records is written contiguously;
 //   pass 2 (k_part_accum), one workgroup per (block, level, slice): sums its
@@ -17,7 +18,7 @@
 //     coalesced rows, so every entry of the slice is written once per step.
 // The LDS sums are 64-bit fixed point: LDS float atomics run at a small
 // fraction of the rate of integer ones on this chip.  Pass 1 records the
-// largest |contribution| of each tile; a bucket of n records whose block's
+// largest |wy wz dL/dy| of each tile, a bound on its contributions; a bucket of n records whose block's
 // largest contribution is M is summed in units of 2^-K with n M 2^K <= 2^62,
 // so no sum can overflow, each contribution is rounded by at most 2^-(K+1)
 // <= n M 2^-63 (far below fp32 rounding of the sums), and the sums do not
@@ -63,45 +64,61 @@ __device__ __forceinline__ int wg_exclusive_scan(int v, int* wsum, int& total) {
   return pre + x - v;
 }
 
-// Records.  Generic F: 1 + F words, (slice << 16 | entry within the slice)
-// then the F fp32 contributions.  F == 2: one 64-bit word — entry within the
-// slice (bits 0..12), exponent e + 127 of the larger |contribution| (bits
-// 13..20; 0 for a zero record), and the two contributions as 21-bit two's-
-// complement mantissas m_i (bits 21..41, 42..62), contribution i = m_i 2^(e-20)
-// with |m_i| < 2^20: each contribution keeps 2^-20 of the pair's larger
-// magnitude (the slice is implied by the bucket).
+// Records.  The two corners of a cell edge along x differ by one in x, so that
+// their entries are e and e ^ (2^f - 1), hashed or dense, and nearly always lie
+// in one slice: one record holds both, as v = wy wz dL/dy and the weight tx of
+// the second corner (the first has 1 - tx).  f = 0: one corner alone, with its
+// whole contribution in v and tx = 0 (the pair crosses slices, or tx is no
+// multiple of 2^-25 below 1: a point within the first quarter of the level's
+// first cell, or on its last plane).
+//   F == 2, 3 words: word 0 entry within the slice (13 bits), f (4), tx 2^25
+//     bits 0..14 (15); word 1 exponent e + 127 of the larger |v| (8; 0 for a
+//     zero record), tx bit 24, v_0 as a 23-bit two's-complement mantissa m_0;
+//     word 2 tx bits 15..23, m_1.  v_i = m_i 2^(e-22) with |m_i| < 2^22, so a
+//     contribution keeps 2^-22 of the pair's larger magnitude and the sums
+//     take m_i tx exactly (the slice is implied by the bucket).
+//   other F, 2 + F words: slice << 20 | f << 16 | entry, tx, v (fp32).
+// Against one record per corner (8 bytes at F = 2) this is half the records
+// to count, place and reserve, and 12 bytes for 16: 64 blocks, 2^20 samples,
+// pass 1 304 -> 256 us; 128^3 fp32, 2^16 samples, 47 -> 40 us and pass 2
+// 70 -> 62 us; one 256^3 block, 2^18 samples, pass 2 98 -> 86 us.
+// Gradient error against 64 bits (3 levels, F 2, 65,536 points on a 2^-17
+// lattice): 1.7 - 3.8e-7 -> 0.66 - 1.5e-7.
 template <int F> struct PartRec {
-  static constexpr int RW = F == 2 ? 2 : 1 + F;  // 32-bit words per record
+  static constexpr int RW = F == 2 ? 3 : 2 + F;  // 32-bit words per record
 };
+constexpr int kTxBits = 25;
+constexpr int kPartStage = 5 * kTile;  // records staged at once (4 per sample, and room for single corners)
 
-__device__ __forceinline__ uint64_t pack_rec2(uint32_t ent, float c0, float c1) {
-  const float a = fmaxf(fabsf(c0), fabsf(c1));
+__device__ __forceinline__ void pack_rec2(uint32_t ent, int f, uint32_t txq, float v0, float v1, uint32_t* w) {
+  const float a = fmaxf(fabsf(v0), fabsf(v1));
   int e = 0;
   (void)frexpf(a, &e);  // a < 2^e
-  if (!(a > 0.0f) || e < -126) return (uint64_t)ent;
-  const float sc = ldexpf(1.0f, 20 - e);
-  const int m0 = max(-(1 << 20) + 1, min((1 << 20) - 1, (int)rintf(c0 * sc)));
-  const int m1 = max(-(1 << 20) + 1, min((1 << 20) - 1, (int)rintf(c1 * sc)));
-  return (uint64_t)ent | ((uint64_t)(e + 127) << 13) | ((uint64_t)((uint32_t)m0 & 0x1FFFFFu) << 21) |
-         ((uint64_t)((uint32_t)m1 & 0x1FFFFFu) << 42);
+  w[0] = ent | ((uint32_t)f << 13) | (txq << 17);
+  w[1] = w[2] = 0u;
+  if (!(a > 0.0f) || e < -126) return;
+  constexpr int kMax = (1 << 22) - 1;
+  const int m0 = max(-kMax, min(kMax, (int)rintf(ldexpf(v0, 22 - e))));
+  const int m1 = max(-kMax, min(kMax, (int)rintf(ldexpf(v1, 22 - e))));
+  w[1] = ((uint32_t)m0 << 9) | (((txq >> 24) & 1u) << 8) | (uint32_t)(e + 127);
+  w[2] = ((uint32_t)m1 << 9) | ((txq >> 15) & 0x1FFu);
 }
 
-// Fields of a packed record: exponent field (0: zero record) and the two mantissas.
-__device__ __forceinline__ void unpack_rec2(uint64_t r, int& ex, int& m0, int& m1) {
-  ex = (int)((r >> 13) & 0xFFu);
-  m0 = ((int)((uint32_t)(r >> 21) << 11)) >> 11;  // sign-extend 21 bits
-  m1 = ((int)((uint32_t)(r >> 42) << 11)) >> 11;
+struct Rec2 {
+  uint32_t ent;
+  int f, ex, txq, m0, m1;  // ex 0: zero record
+};
+__device__ __forceinline__ Rec2 unpack_rec2(uint32_t w0, uint32_t w1, uint32_t w2) {
+  return Rec2{w0 & 0x1FFFu, (int)((w0 >> 13) & 15u), (int)(w1 & 0xFFu),
+              (int)((w0 >> 17) | ((w2 & 0x1FFu) << 15) | (((w1 >> 8) & 1u) << 24)), (int)w1 >> 9, (int)w2 >> 9};
 }
 
-// m 2^s as a 64-bit integer, rounding to nearest when s < 0.
-__device__ __forceinline__ long long shift_fixed(int m, int s) {
-  if (s >= 0) return (long long)m << min(s, 42);  // |m 2^s| <= M 2^K <= 2^62 keeps s <= 42
-  if (s < -40) return 0;
-  return ((long long)m + (1ll << (-s - 1))) >> (-s);
-}
-
+// Bound by the latency of its chain (loads, LDS counts, the bucket atomics, the
+// stage), so by the waves in flight: 8 per SIMD at F <= 2 (64 VGPRs; 7 per SIMD
+// 293 instead of 256 us on the 64-block workload).  The stage holds 5 records a
+// sample, a second round takes what an unusual tile has beyond that.
 template <int F>
-__global__ __launch_bounds__(256) void k_part_bucket(LevelDesc ld, PartDesc pd, const BlockMeta* __restrict__ meta,
+__global__ __launch_bounds__(256, F <= 2 ? 8 : 1) void k_part_bucket(LevelDesc ld, PartDesc pd, const BlockMeta* __restrict__ meta,
                                                      const Tile* __restrict__ tiles, int n_tiles,
                                                      const BlockPlan* __restrict__ plan,
                                                      const PartBlock* __restrict__ pb,
@@ -112,8 +129,8 @@ __global__ __launch_bounds__(256) void k_part_bucket(LevelDesc ld, PartDesc pd, 
                                                      float* __restrict__ grad) {
   constexpr int RW = PartRec<F>::RW;
   constexpr bool PACK = F == 2;
-  __shared__ __align__(16) uint32_t stage[8 * kTile * RW];  // records in slice order
-  __shared__ uint8_t stq[PACK ? 8 * kTile : 1];  // slice of each packed record
+  __shared__ __align__(16) uint32_t stage[kPartStage * RW];  // records in slice order
+  __shared__ uint8_t stq[PACK ? kPartStage : 1];  // slice of each packed record
   __shared__ int hist[kPartMaxSlices], lbase[kPartMaxSlices], gbase[kPartMaxSlices], wsum[4];
   __shared__ float wmax[4];
   const int tid = threadIdx.x;
@@ -127,16 +144,19 @@ __global__ __launch_bounds__(256) void k_part_bucket(LevelDesc ld, PartDesc pd, 
   hist[tid] = 0;
   __syncthreads();
   const bool valid = tid < t.count;
-  uint32_t e[8];
-  float w[8], d[F];
-  int rk[8];
-  float m = 0.0f;  // largest |w * dL/dy| of the lane
+  uint32_t e0[4], e1x = 0, txq = 0;  // first corner of each edge along x, hashed: flip to its second; tx 2^25
+  float w[4], d[F], tx = 0.0f;     // weight of the edge in y and z
+  uint32_t rk[4];                  // rank within the slice (upper half: a split edge's second corner)
+  bool whole = true;               // tx fits a record's field
+  float m = 0.0f;                  // largest |w * dL/dy| of the lane
+  const int dense = ld.dense[l];
+  auto second = [&](uint32_t e) { return dense ? e + 1 : e ^ e1x; };
   if (valid) {
     const int64_t gi = plan[b].sample_off + t.start + tid;
     const int R = ld.R[l];
     const float sc = ld.scale[l];
     int ix, iy, iz;
-    float tx, ty, tz;
+    float ty, tz;
     grid_pos(coords[3 * gi + 0], sc, R, ix, tx);
     grid_pos(coords[3 * gi + 1], sc, R, iy, ty);
     grid_pos(coords[3 * gi + 2], sc, R, iz, tz);
@@ -146,14 +166,21 @@ __global__ __launch_bounds__(256) void k_part_bucket(LevelDesc ld, PartDesc pd, 
       d[f] = dfeat[(int64_t)l * ls + gi * F + f];
       dm = fmaxf(dm, fabsf(d[f]));
     }
-    const int dense = ld.dense[l];
+    if constexpr (PACK) {
+      const float tq = ldexpf(tx, kTxBits);
+      txq = (uint32_t)tq;
+      whole = (float)txq == tq && txq < (1u << kTxBits);
+    }
+    e1x = (uint32_t)(ix ^ (ix + 1)) & ld.T_mask;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t cx = k & 1, cy = (k >> 1) & 1, cz = k >> 2;
-      e[k] = corner_index(dense, R, ld.T_mask, ix + cx, iy + cy, iz + cz);
-      w[k] = (cx ? tx : 1.0f - tx) * (cy ? ty : 1.0f - ty) * (cz ? tz : 1.0f - tz);
-      m = fmaxf(m, w[k] * dm);  // bounds |w * d[f]| for every f (rounding is monotone)
-      rk[k] = atomicAdd(&hist[e[k] >> sh], 1);
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t cy = k & 1, cz = k >> 1;
+      e0[k] = corner_index(dense, R, ld.T_mask, ix, iy + cy, iz + cz);
+      w[k] = (cy ? ty : 1.0f - ty) * (cz ? tz : 1.0f - tz);
+      m = fmaxf(m, w[k] * dm);  // bounds |w * d[f]| for every f (rounding is monotone), and both corners' parts
+      rk[k] = (uint32_t)atomicAdd(&hist[e0[k] >> sh], 1);
+      const uint32_t e1 = second(e0[k]);
+      if (!whole || ((e0[k] ^ e1) >> sh)) rk[k] |= (uint32_t)atomicAdd(&hist[e1 >> sh], 1) << 16;
     }
   }
 #pragma unroll
@@ -169,49 +196,67 @@ __global__ __launch_bounds__(256) void k_part_bucket(LevelDesc ld, PartDesc pd, 
   if (c > 0)
     gbase[tid] = atomicAdd(&cursor[((int64_t)b * pd.nq + pd.qbase[l] + tid) * kPartSub + sub], c);
   __syncthreads();
-  if (valid) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t q = e[k] >> sh;
-      const int i = lbase[q] + rk[k];
-      if constexpr (PACK) {
-        reinterpret_cast<uint64_t*>(stage)[i] = pack_rec2(e[k] & smask, w[k] * d[0], w[k] * d[1]);
-        stq[i] = (uint8_t)q;
-      } else {
-        stage[i * RW] = (q << 16) | (e[k] & smask);
-#pragma unroll
-        for (int f = 0; f < F; ++f) stage[i * RW + 1 + f] = __float_as_uint(w[k] * d[f]);
-      }
-    }
-  }
-  __syncthreads();
   const int64_t off = pb[b].off[l];
   const int cap = pb[b].cap[l];
-  for (int i = tid; i < total; i += 256) {
-    const uint32_t w0 = stage[i * RW];
-    const int q = PACK ? (int)stq[i] : (int)(w0 >> 16);
-    const int j = gbase[q] + i - lbase[q];
-    const int64_t rec = off + ((int64_t)q * pd.nsub + sub) * cap + j;
-    if (j < cap) {
-      if constexpr (PACK) {
-        reinterpret_cast<uint64_t*>(recs)[rec] = reinterpret_cast<const uint64_t*>(stage)[i];
-      } else {
-#pragma unroll
-        for (int k = 0; k < RW; ++k) recs[rec * RW + k] = stage[i * RW + k];
-      }
+  // record i of the tile: entry `ent`, flip f, the second corner's weight and the edge's values
+  auto put = [&](int i, uint32_t ent, int f, float wx, float t1, uint32_t t1q, float wk) {
+    if ((unsigned)i >= (unsigned)kPartStage) return;  // another round's
+    if constexpr (PACK) {
+      pack_rec2(ent & smask, f, t1q, wk * d[0] * wx, wk * d[1] * wx, &stage[i * RW]);
+      stq[i] = (uint8_t)(ent >> sh);
     } else {
-      ovf[(int64_t)b * pd.nq + pd.qbase[l] + q] = 1;
-      float* g = grad + meta[b].param_off + ((int64_t)ld.off[l] + ((int64_t)q << sh) + (w0 & smask)) * F;
-      if constexpr (PACK) {
-        int ex, m0, m1;
-        unpack_rec2(reinterpret_cast<const uint64_t*>(stage)[i], ex, m0, m1);
-        if (ex) {
-          unsafeAtomicAdd(&g[0], ldexpf((float)m0, ex - 147));
-          unsafeAtomicAdd(&g[1], ldexpf((float)m1, ex - 147));
-        }
-      } else {
+      stage[i * RW] = ((ent >> sh) << 20) | ((uint32_t)f << 16) | (ent & smask);
+      stage[i * RW + 1] = __float_as_uint(t1);
 #pragma unroll
-        for (int f = 0; f < F; ++f) unsafeAtomicAdd(&g[f], __uint_as_float(stage[i * RW + 1 + f]));
+      for (int c = 0; c < F; ++c) stage[i * RW + 2 + c] = __float_as_uint(wk * d[c] * wx);
+    }
+  };
+  // one round, unless more than a quarter of the edges are split
+  for (int base = 0; base < total; base += kPartStage) {
+    if (base) __syncthreads();
+    if (valid) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t e1 = second(e0[k]);
+        const int i0 = lbase[e0[k] >> sh] + (int)(rk[k] & 0xFFFFu) - base;
+        const bool split = !whole || ((e0[k] ^ e1) >> sh);
+        put(i0, e0[k], split ? 0 : __popc(e0[k] ^ e1), split ? 1.0f - tx : 1.0f, split ? 0.0f : tx, split ? 0u : txq, w[k]);
+        if (split) put(lbase[e1 >> sh] + (int)(rk[k] >> 16) - base, e1, 0, tx, 0.0f, 0u, w[k]);
+      }
+    }
+    __syncthreads();
+    const int cnt = min(kPartStage, total - base);
+    for (int i = tid; i < cnt; i += 256) {
+      uint32_t r[RW];
+#pragma unroll
+      for (int k = 0; k < RW; ++k) r[k] = stage[i * RW + k];
+      const int q = PACK ? (int)stq[i] : (int)(r[0] >> 20);
+      const int j = gbase[q] + base + i - lbase[q];
+      if (j < cap) {
+        uint32_t* o = recs + (off + ((int64_t)q * pd.nsub + sub) * cap + j) * RW;
+#pragma unroll
+        for (int k = 0; k < RW; ++k) o[k] = r[k];
+      } else {
+        ovf[(int64_t)b * pd.nq + pd.qbase[l] + q] = 1;
+        float* g = grad + meta[b].param_off + ((int64_t)ld.off[l] + ((int64_t)q << sh)) * F;
+        const uint32_t ent = r[0] & (PACK ? 0x1FFFu : 0xFFFFu), f = (r[0] >> (PACK ? 13 : 16)) & 15u;
+        const uint32_t ent1 = ent ^ ((1u << f) - 1u);
+        float v[F], t1 = 0.0f;
+        if constexpr (PACK) {
+          const Rec2 x = unpack_rec2(r[0], r[1], r[2]);
+          v[0] = x.ex ? ldexpf((float)x.m0, x.ex - 149) : 0.0f;
+          v[1] = x.ex ? ldexpf((float)x.m1, x.ex - 149) : 0.0f;
+          t1 = ldexpf((float)x.txq, -kTxBits);
+        } else {
+          t1 = __uint_as_float(r[1]);
+#pragma unroll
+          for (int c = 0; c < F; ++c) v[c] = __uint_as_float(r[2 + c]);
+        }
+#pragma unroll
+        for (int c = 0; c < F; ++c) {
+          unsafeAtomicAdd(&g[(int64_t)ent * F + c], (1.0f - t1) * v[c]);
+          if (f) unsafeAtomicAdd(&g[(int64_t)ent1 * F + c], t1 * v[c]);
+        }
       }
     }
   }
@@ -239,7 +284,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(part_accum_w
                                                     PartAdam adam, int do_adam, uint8_t* __restrict__ ovf) {
   constexpr int RW = PartRec<F>::RW;
   constexpr bool PACK = F == 2;
-  constexpr int U = NT >= 1024 ? 4 : 8;  // records per lane and batch (two batches in flight)
+  constexpr int U = NT >= 1024 ? 2 : 4;  // records per lane and batch (two batches in flight)
   __shared__ unsigned long long acc[SF];
   __shared__ int sstart[kPartSub + 1];
   __shared__ float wmax[NT / 64];
@@ -250,7 +295,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(part_accum_w
   while (l + 1 < pd.l0 + pd.nl && q >= pd.qbase[l + 1]) ++l;
   const int s = q - pd.qbase[l];
   const int sh = pd.sh[l];
-  const uint32_t smask = (1u << sh) - 1u;
   const int cap = pb[b].cap[l];
   // sub-bucket record counts (cursors cleared for the next step's pass 1)
   if (tid < kPartSub) {
@@ -287,7 +331,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(part_accum_w
   (void)frexpf((float)n * M, &E);
   const int K = max(-120, min(120, 62 - E));
   const float scale = ldexpf(1.0f, K);
-  const int kshift = K - 147;  // packed record: contribution i in units 2^-K is m_i 2^(ex - 147 + K)
+  const int kshift = K - 149 - kTxBits;  // packed record: m_i tx 2^25 is in units 2^(ex - 149 - 25)
   const uint32_t* r = recs + (pb[b].off[l] + (int64_t)s * pd.nsub * cap) * RW;
   // a batch of U records per lane from j0 on: unconditional loads (lanes past
   // the end re-read the last record and skip it when summing), so that all of
@@ -303,14 +347,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(part_accum_w
       const uint32_t* rr = r + ((int64_t)g * cap + (j - sstart[g])) * RW;
       // records are read once: non-temporal loads keep them from displacing
       // the volume and table lines the next kernels read from the caches
-      if constexpr (PACK) {
-        const uint64_t t64 = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(rr));
-        v[u][0] = (uint32_t)t64;
-        v[u][1] = (uint32_t)(t64 >> 32);
-      } else {
 #pragma unroll
-        for (int k = 0; k < RW; ++k) v[u][k] = __builtin_nontemporal_load(rr + k);
-      }
+      for (int k = 0; k < RW; ++k) v[u][k] = __builtin_nontemporal_load(rr + k);
     }
   };
   // the slice's elements and its Adam operands (loaded after the record sums:
@@ -403,19 +441,39 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(part_accum_w
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (j0 + u * NT + tid < n) {
-        const uint32_t ent = v[u][0] & smask;
         if constexpr (PACK) {
-          const uint64_t r64 = (uint64_t)v[u][0] | ((uint64_t)v[u][1] << 32);
-          int ex, m0, m1;
-          unpack_rec2(r64, ex, m0, m1);
-          if (ex) {
-            atomicAdd(&acc[ent * 2], (unsigned long long)shift_fixed(m0, ex + kshift));
-            atomicAdd(&acc[ent * 2 + 1], (unsigned long long)shift_fixed(m1, ex + kshift));
+          const Rec2 x = unpack_rec2(v[u][0], v[u][1], v[u][2]);
+          if (x.ex) {
+            // the edge's v splits into tx v and v - tx v, exact in 48 bits, and
+            // both are rounded once to units of 2^-K
+            long long b0 = (long long)x.m0 * x.txq, b1 = (long long)x.m1 * x.txq;
+            long long a0 = ((long long)x.m0 << kTxBits) - b0, a1 = ((long long)x.m1 << kTxBits) - b1;
+            const int sft = x.ex + kshift;
+            if (sft > 0) {  // |m tx| 2^(sft) <= M 2^K <= 2^62 with the larger |m| >= 2^21 keeps sft <= 16
+              const int sl = min(sft, 16);
+              a0 <<= sl, a1 <<= sl, b0 <<= sl, b1 <<= sl;
+            } else {
+              const int sr = min(-sft, 62);
+              const long long half = (1ll << sr) >> 1;
+              a0 = (a0 + half) >> sr, a1 = (a1 + half) >> sr, b0 = (b0 + half) >> sr, b1 = (b1 + half) >> sr;
+            }
+            atomicAdd(&acc[x.ent * 2], (unsigned long long)a0);
+            atomicAdd(&acc[x.ent * 2 + 1], (unsigned long long)a1);
+            if (x.f) {
+              const uint32_t e1 = x.ent ^ ((1u << x.f) - 1u);
+              atomicAdd(&acc[e1 * 2], (unsigned long long)b0);
+              atomicAdd(&acc[e1 * 2 + 1], (unsigned long long)b1);
+            }
           }
         } else {
+          const uint32_t ent = v[u][0] & 0xFFFFu, f = (v[u][0] >> 16) & 15u, e1 = ent ^ ((1u << f) - 1u);
+          const float t1 = __uint_as_float(v[u][1]);
 #pragma unroll
-          for (int f = 0; f < F; ++f)
-            atomicAdd(&acc[ent * F + f], (unsigned long long)__float2ll_rn(__uint_as_float(v[u][1 + f]) * scale));
+          for (int c = 0; c < F; ++c) {
+            const float x = __uint_as_float(v[u][2 + c]);
+            atomicAdd(&acc[ent * F + c], (unsigned long long)__float2ll_rn((1.0f - t1) * x * scale));
+            if (f) atomicAdd(&acc[e1 * F + c], (unsigned long long)__float2ll_rn(t1 * x * scale));
+          }
         }
       }
     }
@@ -561,10 +619,10 @@ hipError_t launch_part_bucket(const LevelDesc& ld, const PartDesc& pd, const Blo
   if (pd.nl <= 0 || n_tiles <= 0) return hipSuccess;
   const int64_t grid = (int64_t)n_tiles * pd.nl;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  // bucket ids fit the LDS histogram and the record's upper 16 bits
+  // bucket ids fit the LDS histogram and, as entries and flips, their fields in a record
   if (pd.nsub < 1 || pd.nsub > kPartSub) return hipErrorInvalidValue;
   for (int l = pd.l0; l < pd.l0 + pd.nl; ++l)
-    if (pd.ns[l] > kPartMaxSlices || pd.sh[l] > 16 || ((int64_t)pd.ns[l] << pd.sh[l]) < pd.E[l])
+    if (pd.ns[l] > kPartMaxSlices || pd.sh[l] > (ld.F == 2 ? 13 : 15) || ((int64_t)pd.ns[l] << pd.sh[l]) < pd.E[l])
       return hipErrorInvalidValue;
   switch (ld.F) {
 #define DVNR_PART_B(FF)                                                                                          \
