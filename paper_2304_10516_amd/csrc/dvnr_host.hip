@@ -60,8 +60,7 @@ struct dvnr {
 
   // current training plan
   int64_t plan_total = -1;
-  std::vector<int64_t> plan_n;  // samples per block of the plan in the workspace
-  bool plan_valid = false;      // it still stands (no option, loss or binding changed since)
+  std::vector<int64_t> plan_n;  // samples per block
   int n_tiles = 0, mlp_grid = 0;
   std::vector<BlockPlan> hplan;
   std::vector<Tile> htiles;
@@ -477,7 +476,6 @@ dvnr_status dvnr_bind(dvnr_t* h, const dvnr_buffers* b) {
     HIPCHK(hipMemset(h->d_ring(), 0, sizeof(float) * kLossRing * h->nb));
     h->host_step = 0;
     h->plan_total = -1;
-    h->plan_valid = false;
     drop_graphs(h);
     h->bound = true;
     h->prepared = false;
@@ -684,18 +682,7 @@ static int table_chunks(const dvnr_t* h, const std::vector<int64_t>& n) {
   return std::max(1, std::min({(int)std::lround(std::sqrt(most) / 4.0), 128, room}));
 }
 
-// The plan (and the step graphs captured on it) stays where the same counts are
-// asked for again, as by one bounded training run after another (16 steps of
-// 65,536 samples: building, uploading and capturing again took 0.2 of 1.6 ms).
 static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_t s) {
-  if (h->plan_valid && n == h->plan_n) {
-    // a plan cannot be built under capture: nor is one used there that happens to stand
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    HIPCHK(hipStreamIsCapturing(s, &cs));
-    if (cs != hipStreamCaptureStatusNone) return fail(DVNR_E_STATE, "a plan is not made while its stream is captured");
-    return DVNR_OK;
-  }
-  h->plan_valid = false;
   int64_t total = 0;
   for (auto v : n) total += v;
   if (total > h->max_batch) return fail(DVNR_E_INVALID, "samples per step exceed max_batch");
@@ -810,7 +797,6 @@ static dvnr_status set_plan(dvnr_t* h, const std::vector<int64_t>& n, hipStream_
   HIPCHK(hipMemcpyAsync(h->d_grange(), h->hgrange.data(), sizeof(int32_t) * 2 * h->nb, hipMemcpyHostToDevice, s));
   HIPCHK(hipStreamSynchronize(s));
   drop_graphs(h);
-  h->plan_valid = true;
   return DVNR_OK;
 }
 
@@ -1775,8 +1761,7 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
       h->spatial_sort = c.sort;
       h->priv_levels = c.priv;
       h->mlp_cap = c.cap;
-      h->plan_valid = false;
-      st = set_plan(h, n, s);
+        st = set_plan(h, n, s);
       if (st) break;
       for (int k = 0; k < 2 && !st; ++k) st = enqueue_step(h, 1, s);
       if (st) break;
@@ -1807,7 +1792,6 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
     h->spatial_sort = pick.sort;
     h->priv_levels = pick.priv;
     h->mlp_cap = pick.cap;
-    h->plan_valid = false;
     st = set_plan(h, n, s);
     if (st) return st;
     h->plan_total = samples_per_step;
@@ -1913,7 +1897,6 @@ dvnr_status dvnr_set_option(dvnr_t* h, const char* name, int64_t value) {
   } else {
     return fail(DVNR_E_INVALID, "unknown option " + n);
   }
-  h->plan_valid = false;
   drop_graphs(h);
   return DVNR_OK;
 }
@@ -1927,7 +1910,6 @@ dvnr_status dvnr_set_loss(dvnr_t* h, int32_t loss, double boundary_frac, double 
   h->bnd_frac = boundary_frac;
   h->bnd_sigma = sigma;
   h->plan_total = -1;  // per-block boundary counts live in the plan
-  h->plan_valid = false;
   drop_graphs(h);
   return DVNR_OK;
 }

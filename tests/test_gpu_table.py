@@ -88,32 +88,3 @@ def test_whole_table_keeps_nonfinite_gradients():
         model.train(1, 2000)
         masks.append(torch.isfinite(model.block_grads(0)[:lay.n_table_params]))
     assert torch.equal(*masks) and not masks[0].all()
-
-
-def test_plan_kept_between_training_calls():
-    """Training calls that find their plan (and its step graph) still standing
-    do what they do on a plan built for them: bounded runs, another sample
-    count, caller-given coordinates and another stream in between.  The two
-    models differ by the order of float atomics alone."""
-    cfg = (o.Encoding(4, 2, 12, 4, 2.0), o.MLP(1, 16))
-    dims = [(32, 30, 28), (17, 32, 9)]
-    coords = torch.rand((700, 3), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
-    seen = []
-    for rebuild in (False, True):
-        _, _, model = _model(cfg, dims)
-        model.set_option("apply_update", 1)
-        streams = [torch.cuda.Stream(), torch.cuda.Stream()]
-        out = []
-        torch.cuda.synchronize()
-        for k in range(6):
-            if rebuild:
-                model.set_option("use_graph", 1)  # any option set: plan and graphs are built again
-            with torch.cuda.stream(streams[k // 3]):
-                steps, _ = model.train_until(4096, min_steps=3 + k % 2, epochs=0, stream=streams[k // 3])
-                out.append(model.train(2, 4096 if k % 3 else 2048, want_loss=True, stream=streams[k // 3]))
-                out.append(model.train_step_coords(coords, [300, 400], stream=streams[k // 3])[None])
-            streams[k // 3].synchronize()
-            assert steps == [3 + k % 2] * 2
-        seen.append(torch.cat(out).cpu())
-    assert torch.isfinite(seen[0]).all()
-    assert float(((seen[0] - seen[1]).abs() / seen[1]).max()) < 1e-3
