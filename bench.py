@@ -86,15 +86,16 @@ def phase_bytes(precision, phase, res):
                    + L x F features written (2 B bf16, 4 B fp32)
     scatter_priv : coords (12) + lp x F dL/dy reads (4 B) + lp x 8 corners x F fp32 gradient adds (4 B)
     scatter      : the same for the nd direct levels
-    part_bucket  : coords (12) + np x F dL/dy reads (4 B) + np x 4 records written, np = L - lf
-                   partitioned levels; a record (one per cell edge along x) is 12 B for F = 2
-                   (packed), (2 + F) x 4 B otherwise
-    part_accum   : np x 4 records read, plus per launch the Adam update of every partitioned
+    part_bucket  : coords (12) + np x F dL/dy reads (4 B) + np x 8 records written, np = L - lf
+                   partitioned levels; a record is 8 B for F = 2 (packed), (1 + F) x 4 B otherwise.
+                   This is the payload with one record per contribution; the passes move
+                   less, 4 records (one per cell edge along x) of 12 B or (2 + F) x 4 B
+    part_accum   : np x 8 records read, plus per launch the Adam update of every partitioned
                    table parameter, which the slice pass applies itself: theta, m, v read and
                    written (24 B) and the fp16 working copy written (2 B, mixed precision)
     adam         : the remaining parameters (34 B each mixed, 32 B fp32)
     """
-    rec = 12 if F_FEAT == 2 else (2 + F_FEAT) * 4
+    rec = 8 if F_FEAT == 2 else (1 + F_FEAT) * 4
     te = 2 if precision == "mixed" else 4
     batch = res["batch"]
     lp, lf = res["priv_levels"], res["part_levels"]
@@ -107,11 +108,11 @@ def phase_bytes(precision, phase, res):
         nl = lp if phase == "scatter_priv" else lf - lp
         return (12 + nl * F_FEAT * 4 + nl * 8 * F_FEAT * 4) * batch if nl > 0 else 0
     if phase == "part_bucket":
-        return (12 + npart * F_FEAT * 4 + npart * 4 * rec) * batch if npart > 0 else 0
+        return (12 + npart * F_FEAT * 4 + npart * 8 * rec) * batch if npart > 0 else 0
     if phase == "part_accum":
         if npart <= 0:
             return 0
-        return npart * 4 * rec * batch + part_params(res) * (26 if precision == "mixed" else 24)
+        return npart * 8 * rec * batch + part_params(res) * (26 if precision == "mixed" else 24)
     if phase == "adam":
         return ADAM_BYTES_PER_PARAM[precision] * (res["n_params"] - part_params(res))
     return None

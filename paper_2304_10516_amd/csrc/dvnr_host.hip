@@ -1761,7 +1761,7 @@ dvnr_status dvnr_autotune(dvnr_t* h, int64_t samples_per_step, int32_t n_trial_s
       h->spatial_sort = c.sort;
       h->priv_levels = c.priv;
       h->mlp_cap = c.cap;
-        st = set_plan(h, n, s);
+      st = set_plan(h, n, s);
       if (st) break;
       for (int k = 0; k < 2 && !st; ++k) st = enqueue_step(h, 1, s);
       if (st) break;
